@@ -29,6 +29,9 @@ UNITS = [
       f"-DVLOC_TUNE_G={gi}"])
     for prec, t in (("f64", "double"), ("f32", "float")) for gi in range(3)
 ] + [
+    ("plane_quads.hip", f"quads_{mode.lower()}.o", [f"-DVLOC_LQ_MODE=MODE_{mode}"])
+    for mode in ("APPLY", "DENSITY", "APPLY_DENSITY")
+] + [
     ("reduce.hip", "reduce.o", []),
     ("plan.cpp", "plan.o", []),
     ("api.cpp", "api.o", []),

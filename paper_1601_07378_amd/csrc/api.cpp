@@ -46,6 +46,7 @@ struct Engine {
     void *d_VT = nullptr;        // potential in the full-plane kernel's order
     void *d_parts = nullptr;     // parted plane: nxo x N2 values per resident workgroup
     Geometry geo{};
+    LaneQuads lq{};
     // kernel timing: events[4*i .. 4*i+3] bracket K1, K2, K3 of launch i
     bool timing = false;
     std::vector<hipEvent_t> events;
@@ -171,6 +172,44 @@ hipError_t upload_vec(V *&dst, const std::vector<V> &src)
     if (e != hipSuccess) return e;
     if (src.empty()) return hipSuccess;
     return hipMemcpy(dst, src.data(), sizeof(V) * src.size(), hipMemcpyHostToDevice);
+}
+
+// Chooses the lane-quad plane kernel for the application and the density (the
+// diagnostic transforms keep the layout's own kernel) where the schedule is
+// automatic and the grid and the occupied x-planes of every member allow it.
+void set_lane_quads(Engine &E, int cus)
+{
+    const Geometry &g = E.geo;
+    const HostPlan &h = *E.members[0];
+    E.lq = LaneQuads{};
+    const vloc_options &o = h.opt;
+    if (o.precision != VLOC_F64 || (h.plane_full != 1 && h.plane_full != 4) || o.plane_xmode ||
+        o.plane_threads || o.plane_rows || o.plane_xwaves || o.split[0] || o.split[1])
+        return;
+    if (std::max(g.L1y, g.L2y) > 16) return;
+    LaneQuads lq{};
+#define VLOC_LQ_HAVE(Q)                                                                            \
+    if (g.N1 == 4 * Q) lq.q = Q;
+    VLOC_LQ_SIZES(VLOC_LQ_HAVE)
+#undef VLOC_LQ_HAVE
+    if (!lq.q) return;
+    lq.cus = cus;
+    lq.planes = 1;
+    lq.zm = lq.lo = lq.hi = ~0u;
+    for (const HostPlan *m : E.members) {
+        // the kernel takes x >= N1 + hmin as one occupied range and 0 <= x <= hmax
+        // as the other, and keeps slots in 16 bits
+        if (m->hmin >= 0 || m->hmax < 0 || m->nst() >= 0xFFFF) return;
+        lq.nxo = std::max(lq.nxo, (int)m->nxo);
+        for (int n = 0; n < lq.q; ++n) {
+            const int a = 4 * n, b = 4 * n + 3, hx = g.N1 + m->hmin; // points a .. b
+            if (!(a > m->hmax && b < hx)) lq.zm &= ~(1u << n);
+            if (!(b <= m->hmax)) lq.lo &= ~(1u << n);
+            if (!(a >= hx)) lq.hi &= ~(1u << n);
+        }
+    }
+    if (lq_lds_bytes(lq.q, g.N2, lq.nxo, 1) > 160 * 1024) return;
+    E.lq = lq;
 }
 
 vloc_status upload(Engine &E)
@@ -341,6 +380,7 @@ vloc_status upload(Engine &E)
             cus = 256;
         const int per_cu = std::max(1, std::min(2, (160 * 1024) / std::max(1, plane_lds(E))));
         g.resident_plane_wgs = cus * per_cu;
+        set_lane_quads(E, cus);
         if (h.plane_full == 4) {
             // one scratch region per workgroup of the persistent plane grid
             const size_t pb = (size_t)g.resident_plane_wgs * h.nxo * h.grid[1] * h.elem_bytes();
@@ -545,7 +585,7 @@ vloc_status run_launches(Engine &E, int mode, const Launch *ls, size_t nl, const
     if ((mode == MODE_APPLY || mode == MODE_APPLY_DENSITY) && g.full && nl > 0) {
         // the potential in the full-plane kernel's order, once per call (with
         // arrange false, VT already holds it)
-        if (arrange && (e = launch_arrange_v<T>(g, V, VT, st)) != hipSuccess)
+        if (arrange && (e = launch_arrange_v<T>(g, E.lq, V, VT, st)) != hipSuccess)
             return hip_fail(e, "potential arrangement launch");
         V = VT;
     }
@@ -562,7 +602,7 @@ vloc_status run_launches(Engine &E, int mode, const Launch *ls, size_t nl, const
             if (e != hipSuccess) return hip_fail(e, "stick forward launch");
         }
         if (timed) (void)hipEventRecord(ev[1], st);
-        e = launch_plane<T>(g, t, L, mode, S, V, psi, band0, h.plane_threads, plane_lds(E), st);
+        e = launch_plane<T>(g, E.lq, t, L, mode, S, V, psi, band0, h.plane_threads, plane_lds(E), st);
         if (e != hipSuccess) return hip_fail(e, "plane launch");
         if (timed) (void)hipEventRecord(ev[2], st);
         if (mode != MODE_G2R && mode != MODE_DENSITY) {
@@ -881,6 +921,15 @@ vloc_status vloc_scale_bands(vloc_plan plan, const void *x, int64_t nbands, cons
 
 namespace {
 
+// Planes that the device's workgroups hold at once in a density pass over
+// `bands` bands.
+int density_planes(const Engine &E, int mode, int64_t bands)
+{
+    if (!E.lq.q) return E.geo.resident_plane_wgs;
+    const LqLaunch l = lq_launch(E.geo, E.lq, mode, bands);
+    return l.resident * l.planes;
+}
+
 // Density passes: checks, band subsets per launch, zeroed FP64 partial planes;
 // then the plane kernel in `mode` (DENSITY or APPLY_DENSITY) and the fixed-order
 // reduction of the partial planes into rho.
@@ -900,7 +949,7 @@ vloc_status density_pass(vloc_plan plan, int mode, const void *c, int64_t nbands
     // band subsets per launch: items N3 * nsub fill the resident workgroups in
     // whole rounds where possible (fewest idle slots, then fewest subsets)
     {
-        const int R = std::max(1, g.resident_plane_wgs);
+        const int R = std::max(1, density_planes(E, mode, chunk));
         const int lo = std::max(1, (R + h.grid[2] - 1) / h.grid[2]);
         int best = lo;
         double best_w = 2.0;
@@ -935,7 +984,7 @@ vloc_status density_pass(vloc_plan plan, int mode, const void *c, int64_t nbands
     if (e != hipSuccess) return hip_fail(e, "fill launch");
     s = dispatch(plan, mode, c, nbands, V, out, w, dchunk);
     if (s != VLOC_OK) return s;
-    e = launch_density_reduce(g, E.d_partial, g.nsub, scale, rho, E.stream);
+    e = launch_density_reduce(g, E.lq, E.d_partial, g.nsub, scale, rho, E.stream);
     return e == hipSuccess ? VLOC_OK : hip_fail(e, "density reduce launch");
 }
 

@@ -1,6 +1,7 @@
 // kernels.hpp -- launch interface of the three transform kernels.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <cstdint>
 
 namespace vloc {
@@ -65,6 +66,17 @@ struct Geometry {
     double inv_n;   // 1 / (N1 N2 N3)
 };
 
+// Lane-quad plane kernel of a plan (application and density; q = 0: the
+// layout's own kernel runs them).
+struct LaneQuads {
+    int q;    // x axis of 4 q points
+    int nxo;  // most occupied x-planes of any segment
+    int cus;  // compute units of the device
+    int planes; // planes per workgroup of the launch
+    unsigned zm, lo, hi; // bit n: points 4 n .. 4 n + 3 unoccupied / occupied with
+                         // x <= hmax / occupied with x >= N1 + hmin, for every segment
+};
+
 // One launch covers the bands of up to kMaxSeg k-points ("segments") that
 // share the grid and the occupied-plane geometry.  Segment s owns launch bands
 // [band_lo, band_lo + nb), its stick buffer at S + s_off ([band][z][slot],
@@ -103,7 +115,7 @@ hipError_t launch_stick_fwd(const Geometry &g, const DevTables &t, const Launch 
 // partial planes; APPLY_DENSITY: both APPLY and DENSITY.  The last three take one segment; psi and the weights are
 // indexed from band band0 (the launch's first band in the caller's arrays).
 template <typename T>
-hipError_t launch_plane(const Geometry &g, const DevTables &t, const Launch &L, int mode, void *S,
+hipError_t launch_plane(const Geometry &g, const LaneQuads &lq, const DevTables &t, const Launch &L, int mode, void *S,
                         const void *V, void *psi, int64_t band0, int threads, int lds_bytes,
                         hipStream_t st);
 // The plane-kernel launchers of the two layouts (whole plane in LDS; occupied
@@ -116,6 +128,71 @@ template <typename T, int MODE>
 hipError_t launch_plane_rows_mode(const Geometry &g, const DevTables &t, const Launch &L, void *S,
                                   const void *V, void *psi, int64_t band0, int threads, int lds,
                                   hipStream_t st);
+// Lane-quad plane kernel (FP64, x pass in registers): application, density, or
+// both.
+template <int MODE>
+hipError_t launch_plane_lq_mode(const Geometry &g, const LaneQuads &lq, const DevTables &t,
+                                const Launch &L, void *S, const void *VT, int64_t band0,
+                                hipStream_t st);
+// Register codelets Q of the lane-quad kernel (x axis of 4 Q points).
+#define VLOC_LQ_SIZES(X)                                                                           \
+    X(8) X(9) X(10) X(12) X(15) X(16) X(18) X(20) X(24) X(25) X(27) X(30) X(32)
+// Waves per SIMD the kernel is compiled for: a lane holds four registers per
+// point of its Q, and in the density alone two more for the sums; y codelets of
+// 15 and 16 points need more than the 128 registers that four waves leave.
+constexpr int lq_wpe(int mode, int q, int ymax)
+{
+    const int groups = (q + 3) / 4;
+    const int regs = 16 * groups + 56 + (mode == MODE_DENSITY ? 8 * groups : 0);
+    const int wpe = regs <= 128 ? 4 : regs <= 168 ? 3 : 2;
+    return ymax > 12 && wpe > 3 ? 3 : wpe;
+}
+inline int lq_ymax(const Geometry &g)
+{
+    return std::max(g.L1y, g.L2y) <= 12 ? 12 : 16;
+}
+// Column stride in LDS: odd, so that lanes along columns fall on distinct banks.
+__host__ __device__ constexpr int lq_ldy(int n2)
+{
+    return n2 | 1;
+}
+inline int lq_lds_bytes(int q, int n2, int nxo, int planes)
+{
+    return (planes * nxo * lq_ldy(n2) + n2 + 3 * q + 1) * 16;
+}
+// Shape of a lane-quad launch over `bands` bands (density: band subsets): planes
+// per workgroup, threads, LDS bytes and resident workgroups.  A wavefront takes
+// a block of 16 rows.  A workgroup's waves are dealt to the four SIMDs in turn
+// from the first, so that one whose waves are no multiple of four leaves slots
+// that the next cannot use (96 rows: six waves; one workgroup per CU at three
+// waves per SIMD): then two planes share a workgroup.  The choice is the least
+// rounds of resident workgroups, times 1 + 0.75 (planes - 1) for their length
+// (96^3: 26.4k cycles for a workgroup of one plane, 46k for one of two).
+struct LqLaunch {
+    int planes, threads, lds, resident;
+};
+inline LqLaunch lq_launch(const Geometry &g, const LaneQuads &lq, int mode, int64_t bands)
+{
+    const int wpe = lq_wpe(mode, lq.q, lq_ymax(g)), cap = 4 * wpe;
+    const int blocks = (g.N2 + 15) / 16;
+    LqLaunch best{};
+    double least = 0.0;
+    for (int p = 1; p <= 4 && (p == 1 || p <= bands); ++p) {
+        const int lds = lq_lds_bytes(lq.q, g.N2, lq.nxo, p);
+        const int units = p * blocks, rounds = (units + cap - 1) / cap;
+        const int waves = (units + rounds - 1) / rounds;
+        if (p > 1 && (lds > 160 * 1024 || rounds > 1)) break;
+        const int per_cu = std::max(1, std::min(160 * 1024 / lds, wpe / ((waves + 3) / 4)));
+        int res = lq.cus * per_cu;
+        if (res >= 8) res &= ~7;
+        const int64_t items = (bands + p - 1) / p * g.N3;
+        const double cost = (double)((items + res - 1) / res) * per_cu * (1.0 + 0.75 * (p - 1));
+        if (p > 1 && cost >= least) continue;
+        least = cost;
+        best = LqLaunch{p, 64 * waves, lds, res};
+    }
+    return best;
+}
 // Compiled specialisations of the whole-plane application kernel for the
 // splits the schedule tuner tries; hit = false where none applies.
 template <typename T>
@@ -134,8 +211,8 @@ hipError_t launch_scale_real(const double *x, int64_t n, const double *scale, do
                              double *y, hipStream_t st);
 // partial planes in [z][y][x] order, or with full != 0 in the full-plane
 // kernel's [z][x][yp] order
-hipError_t launch_density_reduce(const Geometry &g, const double *partial, int nsub,
-                                 const double *scale, double *rho, hipStream_t st);
+hipError_t launch_density_reduce(const Geometry &g, const LaneQuads &lq, const double *partial,
+                                 int nsub, const double *scale, double *rho, hipStream_t st);
 template <typename T>
 hipError_t launch_band_dot(const void *a, const void *b, int64_t npw, int64_t nb, double *out,
                            hipStream_t st);
@@ -148,7 +225,7 @@ hipError_t launch_scale_bands(const void *x, int64_t npw, int64_t nb, const doub
 // VT[z][k1][yp][k2] = V[z][y][k1 + L1x k2] with yp the row's position after the
 // y pass (the full-plane kernel's order of the potential).
 template <typename T>
-hipError_t launch_arrange_v(const Geometry &g, const void *V, void *VT, hipStream_t st);
+hipError_t launch_arrange_v(const Geometry &g, const LaneQuads &lq, const void *V, void *VT, hipStream_t st);
 // K3: stick z-transforms (r -> G direction) with 1/N, gathering into each
 // segment's out.
 template <typename T>

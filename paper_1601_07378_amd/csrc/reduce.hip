@@ -42,9 +42,10 @@ __global__ void k_scale_real(const double *__restrict__ x, long long n,
 
 // rho[j] += scale * inv_n * sum_{s < nsub} partial[s][j'], s ascending, where
 // j = (z, y, x) and j' is j itself, or with full != 0 the full-plane kernel's
-// index (z, x, yp), yp = L2y (y mod L1y) + y / L1y.
+// index (z, x, yp), yp = L2y (y mod L1y) + y / L1y, or with q > 0 the lane-quad
+// kernel's (z, k1, yp, k2), x = k1 + q k2.
 __global__ void k_density_reduce(const double *__restrict__ partial, int nsub, int N1, int N2,
-                                 int N3, int full, int L1y, int L2y, double inv_n,
+                                 int N3, int full, int q, int L1y, int L2y, double inv_n,
                                  const double *__restrict__ scale, double *__restrict__ rho)
 {
     const double f = inv_n * (scale ? scale[0] : 1.0);
@@ -58,7 +59,7 @@ __global__ void k_density_reduce(const double *__restrict__ partial, int nsub, i
             const long long z = zy / N2;
             const int y = (int)(zy - z * N2);
             const int yp = L2y * (y % L1y) + y / L1y;
-            src = (z * N1 + x) * N2 + yp;
+            src = q ? ((z * q + x % q) * N2 + yp) * 4 + x / q : (z * N1 + x) * N2 + yp;
         }
         double acc = 0.0;
         for (int s = 0; s < nsub; ++s) acc += partial[(long long)s * n + src];
@@ -183,13 +184,13 @@ hipError_t launch_scale_real(const double *x, int64_t n, const double *scale, do
     return hipGetLastError();
 }
 
-hipError_t launch_density_reduce(const Geometry &g, const double *partial, int nsub,
-                                 const double *scale, double *rho, hipStream_t st)
+hipError_t launch_density_reduce(const Geometry &g, const LaneQuads &lq, const double *partial,
+                                 int nsub, const double *scale, double *rho, hipStream_t st)
 {
     const int64_t n = (int64_t)g.N1 * g.N2 * g.N3;
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_density_reduce, dim3(grid_for(n)), dim3(256), 0, st, partial, nsub,
-                       g.N1, g.N2, g.N3, g.full, g.L1y, g.L2y, g.inv_n, scale, rho);
+                       g.N1, g.N2, g.N3, g.full, lq.q, g.L1y, g.L2y, g.inv_n, scale, rho);
     return hipGetLastError();
 }
 
