@@ -22,7 +22,7 @@ ARCH = os.environ.get("VLOC_OFFLOAD_ARCH", "gfx950")
 UNITS = [
     ("kernels.hip", f"kernels_{prec}_{part}.o", [f"-DVLOC_ONLY_{prec.upper()}",
                                                  f"-DVLOC_PART_{part.upper()}"])
-    for prec in ("f64", "f32") for part in ("full_apply", "full_aux", "rows", "stick")
+    for prec in ("f64", "f32") for part in ("full_apply", "full_aux", "rows", "stick_fwd", "stick_bwd", "common")
 ] + [
     ("kernels.hip", f"kernels_{prec}_tune{gi}.o",
      [f"-DVLOC_ONLY_{prec.upper()}", "-DVLOC_PART_TUNE", f"-DVLOC_TUNE_T={t}",

@@ -2254,15 +2254,19 @@ void k_plane_quad(Geometry g, DevTables t, Launch L, cx<T> *__restrict__ S,
 // ------------------------------------------------------------ launchers
 //
 // The launchers are compiled in parts, each part once per precision, so that
-// the build runs them in parallel: VLOC_PART_STICK (stick kernels, potential
-// arrangement and the plane-kernel dispatch), VLOC_PART_FULL_APPLY and
+// the build runs them in parallel: VLOC_PART_STICK_FWD and VLOC_PART_STICK_BWD
+// (stick kernels), VLOC_PART_COMMON (potential arrangement and the plane-kernel
+// dispatch), VLOC_PART_FULL_APPLY and
 // VLOC_PART_FULL_AUX (whole-plane kernels of the application, and of the
 // diagnostic transforms and the density) and VLOC_PART_ROWS (row-buffer and
 // lane-quad kernels).  Without a part macro everything but the tuner's
 // specialisations is compiled.
-#if !defined(VLOC_PART_STICK) && !defined(VLOC_PART_FULL_APPLY) &&                               \
+#if !defined(VLOC_PART_STICK_FWD) && !defined(VLOC_PART_STICK_BWD) &&                              \
+    !defined(VLOC_PART_COMMON) && !defined(VLOC_PART_FULL_APPLY) &&                               \
     !defined(VLOC_PART_FULL_AUX) && !defined(VLOC_PART_ROWS) && !defined(VLOC_PART_TUNE)
-#define VLOC_PART_STICK
+#define VLOC_PART_STICK_FWD
+#define VLOC_PART_STICK_BWD
+#define VLOC_PART_COMMON
 #define VLOC_PART_FULL_APPLY
 #define VLOC_PART_FULL_AUX
 #define VLOC_PART_ROWS
@@ -2290,7 +2294,7 @@ void k_plane_quad(Geometry g, DevTables t, Launch L, cx<T> *__restrict__ S,
     return m <= 10 ? 10 : (m <= 12 ? 12 : 0);
 }
 
-#if defined(VLOC_PART_STICK)
+#if defined(VLOC_PART_STICK_FWD) || defined(VLOC_PART_STICK_BWD)
 // Line splits and zero masks compiled as specialisations of the stick
 // kernels; any other plan runs the same kernels with runtime sizes.  A
 // specialisation serves every plan whose zero mask contains its own (it then
@@ -2299,7 +2303,30 @@ void k_plane_quad(Geometry g, DevTables t, Launch L, cx<T> *__restrict__ S,
 #define VLOC_STICK_SPECS(X)                                                                       \
     X(8, 12, 0x38) X(8, 12, 0) X(4, 6, 0x4) X(4, 6, 0) X(8, 16, 0x3C) X(8, 16, 0x38)            \
     X(8, 16, 0) X(8, 10, 0x38) X(8, 10, 0)
+// The planner's splits of the other lengths from 16 to 160: in FP64 with the mask
+// of the groups that a sphere of up to 0.32 of the axis leaves empty, and with
+// none; in FP32 with none only (folding known zeros changes which products the
+// compiler fuses, and FP32 results stay those of the runtime-sized kernels bit
+// for bit).  With runtime sizes the codelets of every length share one kernel
+// (FP64: 128 registers and 76 B per lane spilled backward), and strides and
+// divisors are computed.
+#define VLOC_STICK_LINES(X)                                                                       \
+    X(4, 4) X(3, 6) X(4, 5) X(5, 5) X(3, 9) X(5, 6) X(4, 8) X(6, 6) X(5, 8) X(5, 9) X(6, 8)      \
+    X(5, 10) X(6, 9) X(6, 10) X(8, 8) X(8, 9) X(5, 15) X(9, 9) X(9, 10) X(10, 10) X(9, 12)       \
+    X(10, 12) X(5, 25) X(9, 15) X(12, 12) X(10, 15) X(10, 16)
+template <typename T>
+constexpr int stick_mask(int L1, int L2)
+{
+    if (!std::is_same<T, double>::value) return 0;
+    const int L = L1 * L2;
+    int m = 0;
+    for (int n1 = 0; n1 < L1; ++n1)
+        if (100 * L2 * n1 > 32 * L && 100 * (L2 * n1 + L2 - 1) < 68 * L) m |= 1 << n1;
+    return m;
+}
+#endif
 
+#if defined(VLOC_PART_STICK_FWD)
 template <typename T>
 hipError_t launch_stick_fwd(const Geometry &g, const DevTables &t, const Launch &L, void *S,
                             int threads, hipStream_t st)
@@ -2318,9 +2345,20 @@ hipError_t launch_stick_fwd(const Geometry &g, const DevTables &t, const Launch 
         return g.gamma ? go(k_stick_fwd<T, A, B, Z, true>) : go(k_stick_fwd<T, A, B, Z, false>);
     VLOC_STICK_SPECS(VLOC_K1)
 #undef VLOC_K1
+#define VLOC_K_LINE(A, B)                                                                          \
+    if (g.L1z == A && g.L2z == B) {                                                               \
+        constexpr int M = stick_mask<T>(A, B);                                                    \
+        if ((g.zz & M) == M)                                                                      \
+            return g.gamma ? go(k_stick_fwd<T, A, B, M, true>) : go(k_stick_fwd<T, A, B, M, false>); \
+        return g.gamma ? go(k_stick_fwd<T, A, B, 0, true>) : go(k_stick_fwd<T, A, B, 0, false>);     \
+    }
+    VLOC_STICK_LINES(VLOC_K_LINE)
+#undef VLOC_K_LINE
     return g.gamma ? go(k_stick_fwd<T, 0, 0, 0, true>) : go(k_stick_fwd<T, 0, 0, 0, false>);
 }
+#endif
 
+#if defined(VLOC_PART_STICK_BWD)
 template <typename T>
 hipError_t launch_stick_bwd(const Geometry &g, const DevTables &t, const Launch &L, const void *S,
                             int threads, hipStream_t st)
@@ -2339,9 +2377,18 @@ hipError_t launch_stick_bwd(const Geometry &g, const DevTables &t, const Launch 
         return g.gamma ? go(k_stick_bwd<T, A, B, Z, true>) : go(k_stick_bwd<T, A, B, Z, false>);
     VLOC_STICK_SPECS(VLOC_K3)
 #undef VLOC_K3
+#define VLOC_K_LINE(A, B)                                                                          \
+    if (g.L1z == A && g.L2z == B) {                                                               \
+        constexpr int M = stick_mask<T>(A, B);                                                    \
+        if ((g.zz & M) == M)                                                                      \
+            return g.gamma ? go(k_stick_bwd<T, A, B, M, true>) : go(k_stick_bwd<T, A, B, M, false>); \
+        return g.gamma ? go(k_stick_bwd<T, A, B, 0, true>) : go(k_stick_bwd<T, A, B, 0, false>);     \
+    }
+    VLOC_STICK_LINES(VLOC_K_LINE)
+#undef VLOC_K_LINE
     return g.gamma ? go(k_stick_bwd<T, 0, 0, 0, true>) : go(k_stick_bwd<T, 0, 0, 0, false>);
 }
-#endif // VLOC_PART_STICK
+#endif
 
 #if defined(VLOC_PART_ROWS)
 template <typename T, int MODE, int X1, int X2, int Y1, int Y2, int ZX, int ZY>
@@ -2777,7 +2824,7 @@ hipError_t launch_plane_full_tuned(const Geometry &g, const DevTables &t, const 
 }
 #endif
 
-#if defined(VLOC_PART_STICK)
+#if defined(VLOC_PART_COMMON)
 template <typename T>
 hipError_t launch_plane(const Geometry &g, const LaneQuads &lq, const DevTables &t, const Launch &L, int mode, void *S,
                         const void *V, void *psi, int64_t band0, int threads, int lds_bytes,
@@ -2817,7 +2864,7 @@ hipError_t launch_arrange_v(const Geometry &g, const LaneQuads &lq, const void *
                        g.N3, lq.q ? lq.q : g.L1x, lq.q ? 4 : g.L2x, g.L1y, g.L2y);
     return hipGetLastError();
 }
-#endif // VLOC_PART_STICK
+#endif // VLOC_PART_COMMON
 
 // The build compiles this file once per precision and part (in parallel).
 #define VLOC_PLANE_APPLY(T, F)                                                                    \
@@ -2837,19 +2884,29 @@ hipError_t launch_arrange_v(const Geometry &g, const LaneQuads &lq, const void *
     template hipError_t F<T, MODE_APPLY_DENSITY>(const Geometry &, const DevTables &,             \
                                                  const Launch &, void *, const void *, void *,   \
                                                  int64_t, int, int, hipStream_t);
-#if defined(VLOC_PART_STICK)
-#define VLOC_INSTANTIATE_STICK(T)                                                                 \
+#if defined(VLOC_PART_STICK_FWD)
+#define VLOC_INSTANTIATE_STICK_FWD(T)                                                             \
     template hipError_t launch_stick_fwd<T>(const Geometry &, const DevTables &, const Launch &, \
-                                            void *, int, hipStream_t);                           \
+                                            void *, int, hipStream_t);
+#else
+#define VLOC_INSTANTIATE_STICK_FWD(T)
+#endif
+#if defined(VLOC_PART_STICK_BWD)
+#define VLOC_INSTANTIATE_STICK_BWD(T)                                                             \
     template hipError_t launch_stick_bwd<T>(const Geometry &, const DevTables &, const Launch &, \
-                                            const void *, int, hipStream_t);                     \
+                                            const void *, int, hipStream_t);
+#else
+#define VLOC_INSTANTIATE_STICK_BWD(T)
+#endif
+#if defined(VLOC_PART_COMMON)
+#define VLOC_INSTANTIATE_COMMON(T)                                                                \
     template hipError_t launch_plane<T>(const Geometry &, const LaneQuads &, const DevTables &,  \
                                         const Launch &, int, void *, const void *, void *,       \
                                         int64_t, int, int, hipStream_t);                         \
     template hipError_t launch_arrange_v<T>(const Geometry &, const LaneQuads &, const void *,   \
                                             void *, hipStream_t);
 #else
-#define VLOC_INSTANTIATE_STICK(T)
+#define VLOC_INSTANTIATE_COMMON(T)
 #endif
 #if defined(VLOC_PART_FULL_APPLY)
 #define VLOC_INSTANTIATE_FULL_APPLY(T) VLOC_PLANE_APPLY(T, launch_plane_full_mode)
@@ -2868,8 +2925,8 @@ hipError_t launch_arrange_v(const Geometry &g, const LaneQuads &lq, const void *
 #define VLOC_INSTANTIATE_ROWS(T)
 #endif
 #define VLOC_INSTANTIATE(T)                                                                       \
-    VLOC_INSTANTIATE_STICK(T) VLOC_INSTANTIATE_FULL_APPLY(T) VLOC_INSTANTIATE_FULL_AUX(T)        \
-    VLOC_INSTANTIATE_ROWS(T)
+    VLOC_INSTANTIATE_STICK_FWD(T) VLOC_INSTANTIATE_STICK_BWD(T) VLOC_INSTANTIATE_COMMON(T)       \
+    VLOC_INSTANTIATE_FULL_APPLY(T) VLOC_INSTANTIATE_FULL_AUX(T) VLOC_INSTANTIATE_ROWS(T)
 #if !defined(VLOC_ONLY_F32)
 VLOC_INSTANTIATE(double)
 #endif

@@ -164,10 +164,12 @@ inline int lq_lds_bytes(int q, int n2, int nxo, int planes)
 // per workgroup, threads, LDS bytes and resident workgroups.  A wavefront takes
 // a block of 16 rows.  A workgroup's waves are dealt to the four SIMDs in turn
 // from the first, so that one whose waves are no multiple of four leaves slots
-// that the next cannot use (96 rows: six waves; one workgroup per CU at three
-// waves per SIMD): then two planes share a workgroup.  The choice is the least
-// rounds of resident workgroups, times 1 + 0.75 (planes - 1) for their length
-// (96^3: 26.4k cycles for a workgroup of one plane, 46k for one of two).
+// that the next cannot use (96 rows: six waves, one workgroup per CU at three
+// waves per SIMD).  Several planes share a workgroup where that puts more
+// wavefronts on a CU and shortens the launch: rounds of resident workgroups,
+// times 1 + 0.75 (planes - 1) for a workgroup's time (96^3: 26.4k cycles with one
+// plane, 46k with two).  Where workgroups of one plane fill the CU, they stay:
+// 60 x 60 x 100, 37 bands 90 us, against 101 us with four planes each.
 struct LqLaunch {
     int planes, threads, lds, resident;
 };
@@ -177,6 +179,7 @@ inline LqLaunch lq_launch(const Geometry &g, const LaneQuads &lq, int mode, int6
     const int blocks = (g.N2 + 15) / 16;
     LqLaunch best{};
     double least = 0.0;
+    int most = 0; // wavefronts on a CU
     for (int p = 1; p <= 4 && (p == 1 || p <= bands); ++p) {
         const int lds = lq_lds_bytes(lq.q, g.N2, lq.nxo, p);
         const int units = p * blocks, rounds = (units + cap - 1) / cap;
@@ -186,9 +189,10 @@ inline LqLaunch lq_launch(const Geometry &g, const LaneQuads &lq, int mode, int6
         int res = lq.cus * per_cu;
         if (res >= 8) res &= ~7;
         const int64_t items = (bands + p - 1) / p * g.N3;
-        const double cost = (double)((items + res - 1) / res) * per_cu * (1.0 + 0.75 * (p - 1));
-        if (p > 1 && cost >= least) continue;
+        const double cost = (double)((items + res - 1) / res) * (1.0 + 0.75 * (p - 1));
+        if (p > 1 && (per_cu * waves <= most || cost >= least)) continue;
         least = cost;
+        most = per_cu * waves;
         best = LqLaunch{p, 64 * waves, lds, res};
     }
     return best;
