@@ -582,11 +582,11 @@ vloc_status run_launches(Engine &E, int mode, const Launch *ls, size_t nl, const
     t.wts = wts;
     hipError_t e;
     int64_t band0 = 0;
-    if ((mode == MODE_APPLY || mode == MODE_APPLY_DENSITY) && g.full && nl > 0) {
-        // the potential in the full-plane kernel's order, once per call (with
-        // arrange false, VT already holds it)
-        if (arrange && (e = launch_arrange_v<T>(g, E.lq, V, VT, st)) != hipSuccess)
-            return hip_fail(e, "potential arrangement launch");
+    // the potential in the plane kernel's order, once per call, by the first stick
+    // launch (with arrange false, VT already holds it)
+    const void *Va = nullptr;
+    if ((mode == MODE_APPLY || mode == MODE_APPLY_DENSITY) && g.full) {
+        if (arrange) Va = V;
         V = VT;
     }
     for (size_t li = 0; li < nl; ++li) {
@@ -598,7 +598,8 @@ vloc_status run_launches(Engine &E, int mode, const Launch *ls, size_t nl, const
             (void)hipEventRecord(ev[0], st);
         }
         if (mode != MODE_R2G) {
-            e = launch_stick_fwd<T>(g, t, L, S, h.stick_threads, st);
+            e = launch_stick_fwd<T>(g, E.lq, t, L, S, li == 0 ? Va : nullptr, VT, h.stick_threads,
+                                    st);
             if (e != hipSuccess) return hip_fail(e, "stick forward launch");
         }
         if (timed) (void)hipEventRecord(ev[1], st);

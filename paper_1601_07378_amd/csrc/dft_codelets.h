@@ -103,6 +103,15 @@ __host__ __device__ __forceinline__ void rot(T &xr, T &xi)
     }
 }
 
+__host__ __device__ __forceinline__ double fma_of(double a, double b, double c)
+{
+    return __builtin_fma(a, b, c);
+}
+__host__ __device__ __forceinline__ float fma_of(float a, float b, float c)
+{
+    return __builtin_fmaf(a, b, c);
+}
+
 template <int R, int S, typename T>
 struct Dft;
 
@@ -170,8 +179,10 @@ struct Dft<5, S, T> {
         T a2r = xr[2] + xr[3], a2i = xi[2] + xi[3];
         T b2r = xr[2] - xr[3], b2i = xi[2] - xi[3];
         T x0r = xr[0], x0i = xi[0];
-        T p1r = x0r + c1 * a1r + c2 * a2r, p1i = x0i + c1 * a1i + c2 * a2i;
-        T p2r = x0r + c2 * a1r + c1 * a2r, p2i = x0i + c2 * a1i + c1 * a2i;
+        // (products fused in this order also where x0 is a known zero, so that
+        // kernels that skip zero inputs give the bits of those that do not)
+        T p1r = fma_of(c2, a2r, fma_of(c1, a1r, x0r)), p1i = fma_of(c2, a2i, fma_of(c1, a1i, x0i));
+        T p2r = fma_of(c1, a2r, fma_of(c2, a1r, x0r)), p2i = fma_of(c1, a2i, fma_of(c2, a1i, x0i));
         T q1r = s1 * b1r + s2 * b2r, q1i = s1 * b1i + s2 * b2i; // X1 = p1 + i q1
         T q2r = s2 * b1r - s1 * b2r, q2i = s2 * b1i - s1 * b2i; // X2 = p2 + i q2
         xr[0] = x0r + a1r + a2r; xi[0] = x0i + a1i + a2i;

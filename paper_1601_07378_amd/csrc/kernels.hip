@@ -27,6 +27,40 @@
 
 namespace vloc {
 
+// Potential arrangement, run by the first a.blocks workgroups of a call's first
+// stick launch (the two are independent, and a launch of its own costs 3 to 5 us
+// where the whole call takes 16 to 50): VT[z][k1][yp][k2] = V[z][y][x] with x =
+// k1 + L1x k2 and yp = L2y (y mod L1y) + y / L1y, the order in which the plane
+// kernel's x stage B reads it (each task's L2x values contiguous, tasks along yp
+// adjacent).  One workgroup per (z, block of kArrangeRows consecutive yp): the
+// rows are read whole (coalesced) into LDS, then every (k1, yp, k2) run of the
+// block, kArrangeRows * L2x contiguous values per k1, is written out.
+constexpr int kArrangeRows = 8;
+template <typename T>
+__device__ __forceinline__ void arrange_v(const Geometry &g, const ArrangeV &a,
+                                          unsigned char *smem)
+{
+    const T *__restrict__ V = reinterpret_cast<const T *>(a.V);
+    T *__restrict__ VT = reinterpret_cast<T *>(a.VT);
+    T *rows = reinterpret_cast<T *>(smem); // [kArrangeRows][N1]
+    const int N1 = g.N1, N2 = g.N2, L1y = g.L1y, L2y = g.L2y, L1x = a.L1x, L2x = a.L2x;
+    const int nyb = (N2 + kArrangeRows - 1) / kArrangeRows;
+    const int z = blockIdx.x / nyb, yp0 = (blockIdx.x - z * nyb) * kArrangeRows;
+    const int nr = min(kArrangeRows, N2 - yp0);
+    for (int t = threadIdx.x; t < nr * N1; t += blockDim.x) {
+        const int r = t / N1, x = t - r * N1;
+        const int yp = yp0 + r, y = (yp % L2y) * L1y + yp / L2y;
+        rows[t] = V[((long long)z * N2 + y) * N1 + x];
+    }
+    __syncthreads();
+    const int run = nr * L2x;
+    for (int t = threadIdx.x; t < L1x * run; t += blockDim.x) {
+        const int k1 = t / run, u = t - k1 * run;
+        const int r = u / L2x, k2 = u - r * L2x;
+        VT[(((long long)z * L1x + k1) * N2 + yp0 + r) * L2x + k2] = rows[r * N1 + k1 + L1x * k2];
+    }
+}
+
 // ------------------------------------------------------------------ K1
 // One workgroup per (stick group, band) of a segment.  Stage A loads c
 // straight from HBM (only the stick's own run is non-zero), stage B writes the
@@ -34,12 +68,17 @@ namespace vloc {
 // consecutive slots.
 template <typename T, int CZ1, int CZ2, int ZZ, bool GAM>
 __global__ __launch_bounds__(512) void k_stick_fwd(Geometry g, DevTables t, Launch L,
-                                                   cx<T> *__restrict__ S)
+                                                   cx<T> *__restrict__ S, ArrangeV av)
 {
     extern __shared__ unsigned char smem_raw[];
+    if ((int)blockIdx.x < av.blocks) {
+        arrange_v<T>(g, av, smem_raw);
+        return;
+    }
     cx<T> *lines = reinterpret_cast<cx<T> *>(smem_raw);
-    const Seg sg = seg_by_block(L, blockIdx.x);
-    const int rb = blockIdx.x - sg.blk_lo;
+    const int blk = blockIdx.x - av.blocks;
+    const Seg sg = seg_by_block(L, blk);
+    const int rb = blk - sg.blk_lo;
     const int bl = rb / sg.ngroups, gr = rb - bl * sg.ngroups;
     const int2 gi = t.groups[sg.group_off + gr];
     const int s0 = gi.x, ns = gi.y;
@@ -2211,36 +2250,6 @@ __global__ __launch_bounds__(MAXT) void k_plane_rowblock(Geometry g, DevTables t
     if (ymine && Sprev) y_stage_a2(Sprev);
 }
 
-// VT[z][k1][yp][k2] = V[z][y][x] with x = k1 + L1x k2 and yp = L2y (y mod L1y)
-// + y / L1y: the potential in the order the full-plane kernel's x stage B
-// reads it (each task's L2x values contiguous, tasks along yp adjacent).
-// One workgroup per (z, block of kArrangeRows consecutive yp): the rows are
-// read whole (coalesced) into LDS, then every (k1, yp, k2) run of the block,
-// kArrangeRows * L2x contiguous values per k1, is written out.
-constexpr int kArrangeRows = 8;
-template <typename T>
-__global__ void k_arrange_v(const T *__restrict__ V, T *__restrict__ VT, int N1, int N2, int N3,
-                            int L1x, int L2x, int L1y, int L2y)
-{
-    extern __shared__ unsigned char smem_raw[];
-    T *rows = reinterpret_cast<T *>(smem_raw); // [kArrangeRows][N1]
-    const int nyb = (N2 + kArrangeRows - 1) / kArrangeRows;
-    const int z = blockIdx.x / nyb, yp0 = (blockIdx.x - z * nyb) * kArrangeRows;
-    const int nr = min(kArrangeRows, N2 - yp0);
-    for (int t = threadIdx.x; t < nr * N1; t += blockDim.x) {
-        const int r = t / N1, x = t - r * N1;
-        const int yp = yp0 + r, y = (yp % L2y) * L1y + yp / L2y;
-        rows[t] = V[((long long)z * N2 + y) * N1 + x];
-    }
-    __syncthreads();
-    const int run = nr * L2x;
-    for (int t = threadIdx.x; t < L1x * run; t += blockDim.x) {
-        const int k1 = t / run, u = t - k1 * run;
-        const int r = u / L2x, k2 = u - r * L2x;
-        VT[(((long long)z * L1x + k1) * N2 + yp0 + r) * L2x + k2] = rows[r * N1 + k1 + L1x * k2];
-    }
-}
-
 // Quad variant: no row buffer, so the occupied plane is the only LDS and two
 // workgroups fit on a CU even in FP64; 3 waves per SIMD bound the registers.
 template <typename T, int MODE, int XQ, int CY1, int CY2>
@@ -2255,8 +2264,7 @@ void k_plane_quad(Geometry g, DevTables t, Launch L, cx<T> *__restrict__ S,
 //
 // The launchers are compiled in parts, each part once per precision, so that
 // the build runs them in parallel: VLOC_PART_STICK_FWD and VLOC_PART_STICK_BWD
-// (stick kernels), VLOC_PART_COMMON (potential arrangement and the plane-kernel
-// dispatch), VLOC_PART_FULL_APPLY and
+// (stick kernels), VLOC_PART_COMMON (the plane-kernel dispatch), VLOC_PART_FULL_APPLY and
 // VLOC_PART_FULL_AUX (whole-plane kernels of the application, and of the
 // diagnostic transforms and the density) and VLOC_PART_ROWS (row-buffer and
 // lane-quad kernels).  Without a part macro everything but the tuner's
@@ -2303,41 +2311,39 @@ void k_plane_quad(Geometry g, DevTables t, Launch L, cx<T> *__restrict__ S,
 #define VLOC_STICK_SPECS(X)                                                                       \
     X(8, 12, 0x38) X(8, 12, 0) X(4, 6, 0x4) X(4, 6, 0) X(8, 16, 0x3C) X(8, 16, 0x38)            \
     X(8, 16, 0) X(8, 10, 0x38) X(8, 10, 0)
-// The planner's splits of the other lengths from 16 to 160: in FP64 with the mask
-// of the groups that a sphere of up to 0.32 of the axis leaves empty, and with
-// none; in FP32 with none only (folding known zeros changes which products the
-// compiler fuses, and FP32 results stay those of the runtime-sized kernels bit
-// for bit).  With runtime sizes the codelets of every length share one kernel
-// (FP64: 128 registers and 76 B per lane spilled backward), and strides and
-// divisors are computed.
+// The planner's splits of the other lengths from 16 to 160, without zero masks.
+// With runtime sizes the codelets of every length share one kernel (FP64: 128
+// registers and 76 B per lane spilled backward), and strides and divisors are
+// computed: FP32 90 x 108 x 125, 61 bands, K3 105 -> 61 us; FP32 60^3, 740 bands,
+// the whole application 965 -> 845 us.
 #define VLOC_STICK_LINES(X)                                                                       \
     X(4, 4) X(3, 6) X(4, 5) X(5, 5) X(3, 9) X(5, 6) X(4, 8) X(6, 6) X(5, 8) X(5, 9) X(6, 8)      \
     X(5, 10) X(6, 9) X(6, 10) X(8, 8) X(8, 9) X(5, 15) X(9, 9) X(9, 10) X(10, 10) X(9, 12)       \
     X(10, 12) X(5, 25) X(9, 15) X(12, 12) X(10, 15) X(10, 16)
-template <typename T>
-constexpr int stick_mask(int L1, int L2)
-{
-    if (!std::is_same<T, double>::value) return 0;
-    const int L = L1 * L2;
-    int m = 0;
-    for (int n1 = 0; n1 < L1; ++n1)
-        if (100 * L2 * n1 > 32 * L && 100 * (L2 * n1 + L2 - 1) < 68 * L) m |= 1 << n1;
-    return m;
-}
 #endif
 
 #if defined(VLOC_PART_STICK_FWD)
 template <typename T>
-hipError_t launch_stick_fwd(const Geometry &g, const DevTables &t, const Launch &L, void *S,
-                            int threads, hipStream_t st)
+hipError_t launch_stick_fwd(const Geometry &g, const LaneQuads &lq, const DevTables &t,
+                            const Launch &L, void *S, const void *V, void *VT, int threads,
+                            hipStream_t st)
 {
     if (L.nblk <= 0) return hipSuccess;
     size_t lds = (size_t)g.group_cap * g.ldz * sizeof(cx<T>);
+    ArrangeV av{};
+    if (V) {
+        av.V = V;
+        av.VT = VT;
+        av.blocks = g.N3 * ((g.N2 + kArrangeRows - 1) / kArrangeRows);
+        av.L1x = lq.q ? lq.q : g.L1x;
+        av.L2x = lq.q ? 4 : g.L2x;
+        lds = std::max(lds, (size_t)kArrangeRows * g.N1 * sizeof(T));
+    }
     auto go = [&](auto kern) {
         hipError_t e = allow_lds(kern, lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(L.nblk), dim3(threads), lds, st, g, t, L,
-                           reinterpret_cast<cx<T> *>(S));
+        hipLaunchKernelGGL(kern, dim3((unsigned)av.blocks + (unsigned)L.nblk), dim3(threads), lds,
+                           st, g, t, L, reinterpret_cast<cx<T> *>(S), av);
         return hipGetLastError();
     };
 #define VLOC_K1(A, B, Z)                                                                           \
@@ -2346,12 +2352,8 @@ hipError_t launch_stick_fwd(const Geometry &g, const DevTables &t, const Launch 
     VLOC_STICK_SPECS(VLOC_K1)
 #undef VLOC_K1
 #define VLOC_K_LINE(A, B)                                                                          \
-    if (g.L1z == A && g.L2z == B) {                                                               \
-        constexpr int M = stick_mask<T>(A, B);                                                    \
-        if ((g.zz & M) == M)                                                                      \
-            return g.gamma ? go(k_stick_fwd<T, A, B, M, true>) : go(k_stick_fwd<T, A, B, M, false>); \
-        return g.gamma ? go(k_stick_fwd<T, A, B, 0, true>) : go(k_stick_fwd<T, A, B, 0, false>);     \
-    }
+    if (g.L1z == A && g.L2z == B)                                                                 \
+        return g.gamma ? go(k_stick_fwd<T, A, B, 0, true>) : go(k_stick_fwd<T, A, B, 0, false>);
     VLOC_STICK_LINES(VLOC_K_LINE)
 #undef VLOC_K_LINE
     return g.gamma ? go(k_stick_fwd<T, 0, 0, 0, true>) : go(k_stick_fwd<T, 0, 0, 0, false>);
@@ -2378,12 +2380,8 @@ hipError_t launch_stick_bwd(const Geometry &g, const DevTables &t, const Launch 
     VLOC_STICK_SPECS(VLOC_K3)
 #undef VLOC_K3
 #define VLOC_K_LINE(A, B)                                                                          \
-    if (g.L1z == A && g.L2z == B) {                                                               \
-        constexpr int M = stick_mask<T>(A, B);                                                    \
-        if ((g.zz & M) == M)                                                                      \
-            return g.gamma ? go(k_stick_bwd<T, A, B, M, true>) : go(k_stick_bwd<T, A, B, M, false>); \
-        return g.gamma ? go(k_stick_bwd<T, A, B, 0, true>) : go(k_stick_bwd<T, A, B, 0, false>);     \
-    }
+    if (g.L1z == A && g.L2z == B)                                                                 \
+        return g.gamma ? go(k_stick_bwd<T, A, B, 0, true>) : go(k_stick_bwd<T, A, B, 0, false>);
     VLOC_STICK_LINES(VLOC_K_LINE)
 #undef VLOC_K_LINE
     return g.gamma ? go(k_stick_bwd<T, 0, 0, 0, true>) : go(k_stick_bwd<T, 0, 0, 0, false>);
@@ -2853,17 +2851,6 @@ hipError_t launch_plane(const Geometry &g, const LaneQuads &lq, const DevTables 
     default: return hipErrorInvalidValue;
     }
 }
-
-template <typename T>
-hipError_t launch_arrange_v(const Geometry &g, const LaneQuads &lq, const void *V, void *VT, hipStream_t st)
-{
-    const int nyb = (g.N2 + kArrangeRows - 1) / kArrangeRows;
-    const size_t lds = (size_t)kArrangeRows * g.N1 * sizeof(T);
-    hipLaunchKernelGGL(k_arrange_v<T>, dim3((unsigned)(g.N3 * nyb)), dim3(256), lds, st,
-                       reinterpret_cast<const T *>(V), reinterpret_cast<T *>(VT), g.N1, g.N2,
-                       g.N3, lq.q ? lq.q : g.L1x, lq.q ? 4 : g.L2x, g.L1y, g.L2y);
-    return hipGetLastError();
-}
 #endif // VLOC_PART_COMMON
 
 // The build compiles this file once per precision and part (in parallel).
@@ -2886,8 +2873,9 @@ hipError_t launch_arrange_v(const Geometry &g, const LaneQuads &lq, const void *
                                                  int64_t, int, int, hipStream_t);
 #if defined(VLOC_PART_STICK_FWD)
 #define VLOC_INSTANTIATE_STICK_FWD(T)                                                             \
-    template hipError_t launch_stick_fwd<T>(const Geometry &, const DevTables &, const Launch &, \
-                                            void *, int, hipStream_t);
+    template hipError_t launch_stick_fwd<T>(const Geometry &, const LaneQuads &,                 \
+                                            const DevTables &, const Launch &, void *,           \
+                                            const void *, void *, int, hipStream_t);
 #else
 #define VLOC_INSTANTIATE_STICK_FWD(T)
 #endif
@@ -2902,9 +2890,7 @@ hipError_t launch_arrange_v(const Geometry &g, const LaneQuads &lq, const void *
 #define VLOC_INSTANTIATE_COMMON(T)                                                                \
     template hipError_t launch_plane<T>(const Geometry &, const LaneQuads &, const DevTables &,  \
                                         const Launch &, int, void *, const void *, void *,       \
-                                        int64_t, int, int, hipStream_t);                         \
-    template hipError_t launch_arrange_v<T>(const Geometry &, const LaneQuads &, const void *,   \
-                                            void *, hipStream_t);
+                                        int64_t, int, int, hipStream_t);
 #else
 #define VLOC_INSTANTIATE_COMMON(T)
 #endif

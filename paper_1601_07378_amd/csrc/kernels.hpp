@@ -105,11 +105,21 @@ struct Launch {
     Seg seg[kMaxSeg];
 };
 
+// Arrangement of the potential in the plane kernel's order, next to K1's work.
+struct ArrangeV {
+    const void *V;
+    void *VT;
+    int blocks;   // workgroups that arrange (the first of the launch)
+    int L1x, L2x;
+};
 // K1: stick z-transforms (G -> r direction) from each segment's c into the
-// stick buffer S.
+// stick buffer S.  With V, the launch also writes VT[z][k1][yp][k2] =
+// V[z][y][k1 + L1x k2], yp the row's position after the y pass (the order of the
+// whole-plane, parted and lane-quad kernels).
 template <typename T>
-hipError_t launch_stick_fwd(const Geometry &g, const DevTables &t, const Launch &L, void *S,
-                            int threads, hipStream_t st);
+hipError_t launch_stick_fwd(const Geometry &g, const LaneQuads &lq, const DevTables &t,
+                            const Launch &L, void *S, const void *V, void *VT, int threads,
+                            hipStream_t st);
 // K2: plane kernel over the planes of every segment.  APPLY: S -> S in place.
 // G2R: S -> psi rows; R2G: psi -> S; DENSITY: weighted |psi|^2 into the
 // partial planes; APPLY_DENSITY: both APPLY and DENSITY.  The last three take one segment; psi and the weights are
@@ -226,10 +236,6 @@ template <typename T>
 hipError_t launch_scale_bands(const void *x, int64_t npw, int64_t nb, const double *w,
                               const double *scale, double factor, void *y, hipStream_t st);
 
-// VT[z][k1][yp][k2] = V[z][y][k1 + L1x k2] with yp the row's position after the
-// y pass (the full-plane kernel's order of the potential).
-template <typename T>
-hipError_t launch_arrange_v(const Geometry &g, const LaneQuads &lq, const void *V, void *VT, hipStream_t st);
 // K3: stick z-transforms (r -> G direction) with 1/N, gathering into each
 // segment's out.
 template <typename T>

@@ -89,7 +89,14 @@ def test_lane_quads_vs_oracle_and_whole_plane(grid, R, k, nb):
     assert relerr(rho.cpu().numpy(), rho_old.cpu().numpy()) <= PAIR
 
 
-@pytest.mark.parametrize("grid,R", [((60, 64, 25), 10.0), ((72, 96, 20), 9.0), ((96, 96, 40), 18.0)])
+@pytest.mark.parametrize("grid,R", [
+    ((60, 64, 25), 10.0),
+    ((80, 80, 30), 14.9),    # narrow sphere
+    ((80, 80, 50), 24.9),    # some members within 0.315 of the axis, some not
+    ((100, 40, 40), 19.0),
+    ((72, 96, 20), 9.0),
+    ((96, 96, 50), 24.0),    # the quarter sphere, and shifted ones
+])
 def test_lane_quads_batch_equals_plans(grid, R):
     """Uneven k-points (their own occupied x-planes, odd counts, none) in shared
     launches, band chunks that cut through them, and the plans' own results."""

@@ -1,9 +1,8 @@
 """GPU parity of the stick kernels over the compiled z lengths (every 2-3-5-smooth
-length from 16 to 160): narrow spheres, whose plans take the kernels that skip
-the always-empty groups (FP64), and spheres that reach over 0.32 of the axis, which
-take those without; complex bands at a general k and real bands at Gamma, whose
-pairs also run the splitting step.  Against the CPU oracle, at the per-band gates
-of the other parity tests (FP64 1e-12; FP32 2e-6 on FP32-rounded inputs)."""
+length from 16 to 160): narrow spheres and ones that reach over 0.4 of the axis,
+complex bands at a general k and real bands at Gamma, whose pairs also run the
+splitting step.  Against the CPU oracle, at the per-band gates of the other parity
+tests (FP64 1e-12; FP32 2e-6 on FP32-rounded inputs)."""
 import numpy as np
 import pytest
 
