@@ -378,7 +378,11 @@ vloc_status upload(Engine &E)
                 hipSuccess ||
             cus < 1)
             cus = 256;
-        const int per_cu = std::max(1, std::min(2, (160 * 1024) / std::max(1, plane_lds(E))));
+        const int fit = (160 * 1024) / std::max(1, plane_lds(E));
+        int per_cu = std::max(1, std::min(2, fit));
+        // narrow workgroups: as many as fill the 16 waves that 128 registers leave
+        const int lt = plane_launch_threads(g, h.plane_threads);
+        if (lt < h.plane_threads) per_cu = std::max(per_cu, std::min(fit, 1024 / lt));
         g.resident_plane_wgs = cus * per_cu;
         set_lane_quads(E, cus);
         if (h.plane_full == 4) {

@@ -1431,6 +1431,15 @@ __device__ __forceinline__ void plane_full_body(const Geometry &g, const DevTabl
     }
 }
 
+// Waves per SIMD that the kernel leaves registers for, where more than its own
+// workgroup needs: two FP32 workgroups of 768 threads share a CU (12 waves each,
+// three on every SIMD), at 80 registers.
+template <typename T>
+constexpr int plane_full_wpe(int maxt)
+{
+    return std::is_same<T, float>::value && maxt == 768 ? 6 : 1;
+}
+
 // YT > 0: the direct y form with up to YT y tasks per thread (chosen by the
 // launcher when the geometry allows it; a separate instantiation, so that the
 // scatter form does not carry its registers)
@@ -1440,7 +1449,7 @@ __device__ __forceinline__ void plane_full_body(const Geometry &g, const DevTabl
 // most DA of them)
 template <typename T, int MODE, int CX1, int CX2, int CY1, int CY2, int ZX, int FX, int ZY,
           int MAXT, bool WPR, int YT, int GMR = 0, int DA = 0>
-__global__ __launch_bounds__(MAXT) void k_plane_full(Geometry g, DevTables t, Launch L,
+__global__ __launch_bounds__(MAXT, plane_full_wpe<T>(MAXT)) void k_plane_full(Geometry g, DevTables t, Launch L,
                                                      cx<T> *__restrict__ S,
                                                      const T *__restrict__ VT,
                                                      cx<T> *__restrict__ psi, long long band0)
@@ -2488,6 +2497,7 @@ static hipError_t launch_plane_full(const Geometry &g, const DevTables &t, const
                                     ((MODE == MODE_DENSITY || MODE == MODE_APPLY_DENSITY) &&
                                      std::is_same<T, float>::value));
     const bool dyok = DYK && L.nseg == 1;
+    const int lt = plane_launch_threads(g, threads);
     auto pick = [&](auto wpr) {
         constexpr bool W = decltype(wpr)::value;
         constexpr int G = W ? 0 : GMR;
@@ -2497,24 +2507,24 @@ static hipError_t launch_plane_full(const Geometry &g, const DevTables &t, const
         if constexpr (std::is_same<T, double>::value &&
                       (MODE == MODE_APPLY || MODE == MODE_DENSITY ||
                        MODE == MODE_APPLY_DENSITY)) {
-            const bool dy1 = !W && dyok && L.seg[0].nxo * g.L2y <= threads;
+            const bool dy1 = !W && dyok && L.seg[0].nxo * g.L2y <= lt;
             if (threads > 512 && plane_codelet_max(g) > 16) return hipErrorInvalidValue;
             if (threads > 768) {
                 if constexpr (DYK && !W)
                     if (dy1)
                         return go(k_plane_full<T, MODE, X1, X2, Y1, Y2, ZX, FX, ZY, 1024, W, 1, G>,
-                                  threads);
-                return go(k_plane_full<T, MODE, X1, X2, Y1, Y2, ZX, FX, ZY, 1024, W, 0, G>, threads);
+                                  lt);
+                return go(k_plane_full<T, MODE, X1, X2, Y1, Y2, ZX, FX, ZY, 1024, W, 0, G>, lt);
             }
             if (threads > 512) {
                 if constexpr (DYK && !W)
                     if (dy1)
                         return go(k_plane_full<T, MODE, X1, X2, Y1, Y2, ZX, FX, ZY, 768, W, 1, G>,
-                                  threads);
-                return go(k_plane_full<T, MODE, X1, X2, Y1, Y2, ZX, FX, ZY, 768, W, 0, G>, threads);
+                                  lt);
+                return go(k_plane_full<T, MODE, X1, X2, Y1, Y2, ZX, FX, ZY, 768, W, 0, G>, lt);
             }
         }
-        const int nt = threads < 512 ? threads : 512;
+        const int nt = lt < 512 ? lt : 512;
         // FP32 density with a plane that leaves one workgroup per CU: 1024
         // threads (128 registers each), one x stage-B task per thread, and the
         // density sums of a work item held in registers; the y passes in the
@@ -2533,12 +2543,31 @@ static hipError_t launch_plane_full(const Geometry &g, const DevTables &t, const
             if (2LL * lds > 160 * 1024 && threads >= 512 && dyok &&
                 L.seg[0].nxo * g.L2y <= 1024)
                 return go(k_plane_full<T, MODE, X1, X2, Y1, Y2, ZX, FX, ZY, 1024, W, 1, G>, 1024);
+        constexpr bool F768 = std::is_same<T, float>::value && X1 * Y2 > 0 &&
+                              8LL * X1 * X2 * Y1 * Y2 <= 80 * 1024 && X1 * X2 * Y1 * Y2 > 4096 &&
+                              (MODE == MODE_APPLY || MODE == MODE_DENSITY);
         // the same for the runtime-sized FP32 application (codelets of at most
         // 16 points, scatter y form)
         if constexpr (std::is_same<T, float>::value && MODE == MODE_APPLY && X1 == 0 && !W)
             if (2LL * lds > 160 * 1024 && threads >= 512 && plane_codelet_max(g) <= 16)
                 return go(k_plane_full<T, MODE, 0, 0, 0, 0, 0, 0, 0, 1024, W, 0, G ? G : 16>,
                           1024);
+        // compiled FP32 planes of which two fit a CU: 768 threads each, so that 24
+        // waves instead of 16 hide the latencies of the stages (96^3 x 256 bands,
+        // K2 516 -> 471 us; 72 x 96 x 128, four k-points of 64 - 512 bands, 1987 ->
+        // 1885 us; the density of 80^3 and 96^3, whole calls, 527 -> 456 and 595 ->
+        // 516 us).  640 and 896 threads leave one workgroup per CU (their waves are
+        // no multiple of four: 669 and 663 us), 1024 spill, and so does application
+        // and density in one pass (28 registers; 941 -> 962 us), which keeps 512.
+        // Planes of up to 4096 points have no tasks for 768 threads (24^3 1148 ->
+        // 1232 us).
+        if constexpr (F768 && !W)
+            if (2LL * lds <= 160 * 1024 && threads >= 512) {
+                if constexpr (DYK)
+                    if (dyok && L.seg[0].nxo * g.L2y <= 768)
+                        return go(k_plane_full<T, MODE, X1, X2, Y1, Y2, ZX, FX, ZY, 768, W, 1, G>,
+                                  768);
+            }
         if constexpr (DYK && !W && std::is_same<T, float>::value)
             if (dyok && L.seg[0].nxo * g.L2y <= 2 * nt)
                 return go(k_plane_full<T, MODE, X1, X2, Y1, Y2, ZX, FX, ZY, 512, W, 2, G>, nt);

@@ -66,6 +66,16 @@ struct Geometry {
     double inv_n;   // 1 / (N1 N2 N3)
 };
 
+// Threads of a whole-plane launch: no more than the plane's widest stage has
+// tasks for, in steps of four waves (one per SIMD).  24^3 (144 tasks): 256 instead
+// of 512 or 1024 threads, and as many more workgroups per CU.
+inline int plane_launch_threads(const Geometry &g, int threads)
+{
+    if (g.full != 1) return threads;
+    const int tasks = std::max(g.nxo * std::max(g.L1y, g.L2y), g.N2 * std::max(g.L1x, g.L2x));
+    return std::min(threads, std::max(256, (tasks + 255) / 256 * 256));
+}
+
 // Lane-quad plane kernel of a plan (application and density; q = 0: the
 // layout's own kernel runs them).
 struct LaneQuads {

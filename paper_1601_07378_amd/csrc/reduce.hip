@@ -40,30 +40,58 @@ __global__ void k_scale_real(const double *__restrict__ x, long long n,
         y[i] = f * x[i];
 }
 
-// rho[j] += scale * inv_n * sum_{s < nsub} partial[s][j'], s ascending, where
-// j = (z, y, x) and j' is j itself, or with full != 0 the full-plane kernel's
-// index (z, x, yp), yp = L2y (y mod L1y) + y / L1y, or with q > 0 the lane-quad
-// kernel's (z, k1, yp, k2), x = k1 + q k2.
-__global__ void k_density_reduce(const double *__restrict__ partial, int nsub, int N1, int N2,
-                                 int N3, int full, int q, int L1y, int L2y, double inv_n,
-                                 const double *__restrict__ scale, double *__restrict__ rho)
+// rho[j] += scale * inv_n * sum_{s < nsub} partial[s][j], s ascending, for partial
+// planes in the order of rho (z, y, x).
+__global__ void k_density_reduce(const double *__restrict__ partial, int nsub, long long n,
+                                 double inv_n, const double *__restrict__ scale,
+                                 double *__restrict__ rho)
 {
     const double f = inv_n * (scale ? scale[0] : 1.0);
-    const long long n = (long long)N1 * N2 * N3;
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
          i += (long long)gridDim.x * blockDim.x) {
-        long long src = i;
-        if (full) {
-            const long long zy = i / N1;
-            const int x = (int)(i - zy * N1);
-            const long long z = zy / N2;
-            const int y = (int)(zy - z * N2);
-            const int yp = L2y * (y % L1y) + y / L1y;
-            src = q ? ((z * q + x % q) * N2 + yp) * 4 + x / q : (z * N1 + x) * N2 + yp;
+        double acc = 0.0;
+        for (int s = 0; s < nsub; ++s) acc += partial[(long long)s * n + i];
+        rho[i] += f * acc;
+    }
+}
+
+// The same for partial planes in a plane kernel's order: (z, x, yp), yp = L2y (y mod
+// L1y) + y / L1y, or with q > 0 the lane-quad kernel's (z, k1, yp, k2), x = k1 + q k2.
+// One workgroup per z and ty rows yp: the partial planes are read along yp (runs
+// of ty or 4 ty values), the sums turned in LDS, and rho updated along x, so that
+// neither side touches a line for one value of it (128^3, two subsets: 36 -> 14 us).
+__global__ __launch_bounds__(256) void k_density_reduce_rows(
+    const double *__restrict__ partial, int nsub, int N1, int N2, int N3, int ty, int q, int L1y,
+    int L2y, double inv_n, const double *__restrict__ scale, double *__restrict__ rho)
+{
+    extern __shared__ double tile[]; // [x][ty + 1]
+    const double f = inv_n * (scale ? scale[0] : 1.0);
+    const long long n = (long long)N1 * N2 * N3;
+    const int nyb = (N2 + ty - 1) / ty;
+    const int z = blockIdx.x / nyb, yp0 = (blockIdx.x - z * nyb) * ty;
+    const int nr = min(ty, N2 - yp0);
+    for (int i = threadIdx.x; i < N1 * nr; i += blockDim.x) {
+        int x, r;
+        long long src;
+        if (q) {
+            const int k2 = i & 3, v = i >> 2, k1 = v / nr;
+            r = v - k1 * nr;
+            x = k1 + q * k2;
+            src = (((long long)z * q + k1) * N2 + yp0 + r) * 4 + k2;
+        } else {
+            x = i / nr;
+            r = i - x * nr;
+            src = ((long long)z * N1 + x) * N2 + yp0 + r;
         }
         double acc = 0.0;
         for (int s = 0; s < nsub; ++s) acc += partial[(long long)s * n + src];
-        rho[i] += f * acc;
+        tile[x * (ty + 1) + r] = acc;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < N1 * nr; i += blockDim.x) {
+        const int r = i / N1, x = i - r * N1;
+        const int yp = yp0 + r, y = (yp % L2y) * L1y + yp / L2y;
+        rho[((long long)z * N2 + y) * N1 + x] += f * tile[x * (ty + 1) + r];
     }
 }
 
@@ -189,8 +217,16 @@ hipError_t launch_density_reduce(const Geometry &g, const LaneQuads &lq, const d
 {
     const int64_t n = (int64_t)g.N1 * g.N2 * g.N3;
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_density_reduce, dim3(grid_for(n)), dim3(256), 0, st, partial, nsub,
-                       g.N1, g.N2, g.N3, g.full, lq.q, g.L1y, g.L2y, g.inv_n, scale, rho);
+    if (g.full) {
+        // at most 64 KiB of LDS
+        const int ty = g.N1 <= 480 ? 16 : 4;
+        hipLaunchKernelGGL(k_density_reduce_rows, dim3((unsigned)(g.N3 * ((g.N2 + ty - 1) / ty))),
+                           dim3(256), (size_t)g.N1 * (ty + 1) * sizeof(double), st, partial, nsub,
+                           g.N1, g.N2, g.N3, ty, lq.q, g.L1y, g.L2y, g.inv_n, scale, rho);
+    } else {
+        hipLaunchKernelGGL(k_density_reduce, dim3(grid_for(n)), dim3(256), 0, st, partial, nsub,
+                           (long long)n, g.inv_n, scale, rho);
+    }
     return hipGetLastError();
 }
 
