@@ -29,6 +29,12 @@ UNITS = [
       f"-DVLOC_TUNE_G={gi}"])
     for prec, t in (("f64", "double"), ("f32", "float")) for gi in range(3)
 ] + [
+    ("kernels.hip", f"kernels_{prec}_xline_{mode.lower()}.o",
+     [f"-DVLOC_ONLY_{prec.upper()}", "-DVLOC_PART_XLINE", f"-DVLOC_XLINE_T={t}",
+      f"-DVLOC_XLINE_MODE=MODE_{mode}"])
+    for prec, t in (("f64", "double"), ("f32", "float"))
+    for mode in ("APPLY", "DENSITY", "APPLY_DENSITY")
+] + [
     ("plane_quads.hip", f"quads_{mode.lower()}.o", [f"-DVLOC_LQ_MODE=MODE_{mode}"])
     for mode in ("APPLY", "DENSITY", "APPLY_DENSITY")
 ] + [

@@ -195,11 +195,25 @@ void set_lane_quads(Engine &E, int cus)
     if (!lq.q) return;
     lq.cus = cus;
     lq.planes = 1;
+    // classes by the reach |h + k| <= ext of the sphere on the x and y axes, which the
+    // k-points of a batch share
+    auto reach = [&](int axis) {
+        const double *a = h.cell + 3 * axis;
+        return std::sqrt(2.0 * h.ecut * (a[0] * a[0] + a[1] * a[1] + a[2] * a[2])) /
+               6.283185307179586476925;
+    };
+    const double ex = reach(0), ey = reach(1), tol = 1e-9 * g.N1;
+    lq.cls = ex >= g.N1 / 4.0 - 1.0 && ex <= g.N1 / 4.0 + tol ? 2
+             : ex >= 0.19 * g.N1 && ex <= 0.32 * g.N1         ? 1
+                                                              : 0;
+    lq.ynarrow = ey <= 0.29 * g.N2;
     lq.zm = lq.lo = lq.hi = ~0u;
     for (const HostPlan *m : E.members) {
         // the kernel takes x >= N1 + hmin as one occupied range and 0 <= x <= hmax
         // as the other, and keeps slots in 16 bits
         if (m->hmin >= 0 || m->hmax < 0 || m->nst() >= 0xFFFF) return;
+        if (std::abs(m->kpt[0]) > 1.0) lq.cls = 0;
+        if (std::abs(m->kpt[1]) > 1.0) lq.ynarrow = 0;
         lq.nxo = std::max(lq.nxo, (int)m->nxo);
         for (int n = 0; n < lq.q; ++n) {
             const int a = 4 * n, b = 4 * n + 3, hx = g.N1 + m->hmin; // points a .. b

@@ -2280,7 +2280,8 @@ void k_plane_quad(Geometry g, DevTables t, Launch L, cx<T> *__restrict__ S,
 // specialisations is compiled.
 #if !defined(VLOC_PART_STICK_FWD) && !defined(VLOC_PART_STICK_BWD) &&                              \
     !defined(VLOC_PART_COMMON) && !defined(VLOC_PART_FULL_APPLY) &&                               \
-    !defined(VLOC_PART_FULL_AUX) && !defined(VLOC_PART_ROWS) && !defined(VLOC_PART_TUNE)
+    !defined(VLOC_PART_FULL_AUX) && !defined(VLOC_PART_ROWS) && !defined(VLOC_PART_TUNE) &&       \
+    !defined(VLOC_PART_XLINE)
 #define VLOC_PART_STICK_FWD
 #define VLOC_PART_STICK_BWD
 #define VLOC_PART_COMMON
@@ -2293,6 +2294,14 @@ void k_plane_quad(Geometry g, DevTables t, Launch L, cx<T> *__restrict__ S,
 #if defined(VLOC_PART_FULL_APPLY) || defined(VLOC_PART_FULL_AUX)
 #define VLOC_PART_FULL
 #endif
+
+// Compiled splits and zero masks {L1x, L2x, L1y, L2y, zx, fx, zy} of the whole-plane
+// kernel (a specialisation serves every plan whose masks contain its own).
+#define VLOC_FULL_SPECS(X)                                                                        \
+    X(8, 12, 8, 12, 0x38, 0xC3, 0x38) X(12, 8, 8, 12, 0x1F0, 0xE07, 0x38) \
+    X(8, 9, 8, 12, 0x38, 0xC3, 0x3C) X(8, 16, 8, 16, 0x38, 0xC3, 0x38) \
+    X(8, 16, 16, 8, 0x38, 0xC3, 0xFE0) X(8, 10, 8, 10, 0x38, 0xC3, 0x38) \
+    X(4, 6, 4, 6, 0x4, 0x9, 0x4)
 
 // Largest codelet of the plane kernel's x and y splits: kernels of more than
 // 512 threads are compiled for codelets of at most 16 points.
@@ -2682,13 +2691,7 @@ hipError_t launch_plane_full_mode(const Geometry &g, const DevTables &t, const L
         (g.fx & FX) == FX && (g.zy & ZY) == ZY)                                                   \
         return launch_plane_full<T, MODE, X1, X2, Y1, Y2, ZX, FX, ZY>(g, t, L, S, V, psi, band0,   \
                                                                      threads, lds, st);
-    VLOC_FULL_CASE(8, 12, 8, 12, 0x38, 0xC3, 0x38)
-    VLOC_FULL_CASE(12, 8, 8, 12, 0x1F0, 0xE07, 0x38)
-    VLOC_FULL_CASE(8, 9, 8, 12, 0x38, 0xC3, 0x3C)
-    VLOC_FULL_CASE(8, 16, 8, 16, 0x38, 0xC3, 0x38)
-    VLOC_FULL_CASE(8, 16, 16, 8, 0x38, 0xC3, 0xFE0)
-    VLOC_FULL_CASE(8, 10, 8, 10, 0x38, 0xC3, 0x38)
-    VLOC_FULL_CASE(4, 6, 4, 6, 0x4, 0x9, 0x4)
+    VLOC_FULL_SPECS(VLOC_FULL_CASE)
 #undef VLOC_FULL_CASE
     if constexpr (MODE == MODE_APPLY) {
         bool hit = false;
@@ -2708,6 +2711,82 @@ hipError_t launch_plane_full_mode(const Geometry &g, const DevTables &t, const L
     }
 }
 #endif // VLOC_PART_FULL
+
+#if defined(VLOC_PART_XLINE)
+// Whole-plane kernels with the x split compiled and the y split at run time (y
+// codelets of at most 12 points): the planner's x splits with codelets of that size,
+// for spheres of at least 0.36 of the x axis (any other plan runs the runtime-sized
+// kernel).  No zero masks: folding known zeros changes which products the compiler
+// fuses, and these kernels keep the bits of the runtime-sized ones, so that a
+// batch member equals its own plan whichever of them runs.  The x pass is two thirds
+// of a plane's arithmetic, so most of what both compiled splits give: whole
+// applications FP32 60^3 x 555 bands 634 -> 568 us, 90 x 108 x 125 x 61 382 -> 367 us,
+// FP64 50^3 x 960 930 -> 889 us.  FP64 planes of an x axis that the lane-quad kernel
+// covers never get here.
+#define VLOC_XLINES(X)                                                                             \
+    X(3, 6) X(4, 5) X(4, 6) X(5, 5) X(3, 9) X(5, 6) X(5, 9) X(5, 10) X(6, 9) X(9, 9) X(9, 10)
+#define VLOC_XLINES_F64(X)                                                                         \
+    VLOC_XLINES(X) X(12, 12)
+#define VLOC_XLINES_F32(X)                                                                         \
+    VLOC_XLINES(X) X(4, 8) X(6, 6) X(5, 8) X(6, 8) X(6, 10) X(8, 8) X(8, 9) X(8, 10)           \
+    X(8, 12) X(10, 10) X(9, 12) X(10, 12)
+// Stage-A groups that every sphere of at least 0.36 of the axis occupies whole.
+constexpr int xline_full(int L1, int L2)
+{
+    const int L = L1 * L2;
+    int m = 0;
+    for (int n1 = 0; n1 < L1; ++n1)
+        if (100 * (L2 * n1 + L2 - 1) <= 18 * L || 100 * L2 * n1 >= 82 * L) m |= 1 << n1;
+    return m;
+}
+
+template <typename T, int MODE, int X1, int X2, int MAXT>
+static hipError_t launch_xline(const Geometry &g, const DevTables &t, const Launch &L, void *S,
+                               const void *VT, int64_t band0, int threads, int lds, hipStream_t st)
+{
+    auto kern = k_plane_full<T, MODE, X1, X2, 0, 0, 0, xline_full(X1, X2), 0, MAXT, false, 0, 12>;
+    hipError_t e = allow_lds(kern, (size_t)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(plane_blocks(g, L.nbt)), dim3(threads), (size_t)lds, st, g, t, L,
+                       reinterpret_cast<cx<T> *>(S), reinterpret_cast<const T *>(VT),
+                       (cx<T> *)nullptr, (long long)band0);
+    return hipGetLastError();
+}
+
+template <typename T, int MODE>
+hipError_t launch_plane_xline(const Geometry &g, const DevTables &t, const Launch &L, void *S,
+                              const void *VT, int64_t band0, int threads, int lds,
+                              hipStream_t st, bool &hit)
+{
+    if (!plane_codelet_class(g)) return hipSuccess;
+    const int lt = plane_launch_threads(g, threads);
+    constexpr bool F32 = std::is_same<T, float>::value;
+    // FP32 application with one workgroup per CU: 1024 threads, as at runtime sizes
+    const bool wide = F32 && MODE == MODE_APPLY && 2LL * lds > 160 * 1024 && threads >= 512;
+#define VLOC_XLINE_CASE(X1, X2)                                                                    \
+    if (g.L1x == X1 && g.L2x == X2) {                                                              \
+        constexpr int F = xline_full(X1, X2);                                                      \
+        if ((g.fx & F) != F) return hipSuccess;                                                    \
+        hit = true;                                                                                \
+        if constexpr (F32 && MODE == MODE_APPLY && X1 * X2 >= 60)                                  \
+            if (wide) return launch_xline<T, MODE, X1, X2, 1024>(g, t, L, S, VT, band0, 1024, lds, \
+                                                                 st);                              \
+        return launch_xline<T, MODE, X1, X2, F32 ? 512 : 1024>(g, t, L, S, VT, band0,              \
+                                                               F32 ? std::min(lt, 512) : lt, lds,  \
+                                                               st);                                \
+    }
+    if constexpr (F32) {
+        VLOC_XLINES_F32(VLOC_XLINE_CASE)
+    } else {
+        VLOC_XLINES_F64(VLOC_XLINE_CASE)
+    }
+#undef VLOC_XLINE_CASE
+    return hipSuccess;
+}
+template hipError_t launch_plane_xline<VLOC_XLINE_T, VLOC_XLINE_MODE>(
+    const Geometry &, const DevTables &, const Launch &, void *, const void *, int64_t, int, int,
+    hipStream_t, bool &);
+#endif // VLOC_PART_XLINE
 
 #if defined(VLOC_PART_TUNE)
 // Compiled specialisations for the schedule tuner: every split of the x and y
@@ -2852,6 +2931,18 @@ hipError_t launch_plane_full_tuned(const Geometry &g, const DevTables &t, const 
 #endif
 
 #if defined(VLOC_PART_COMMON)
+// Does a specialisation of both splits run this plan (or may one of the tuner's)?
+static bool full_spec(const Geometry &g)
+{
+#define VLOC_FULL_HAVE(X1, X2, Y1, Y2, ZX, FX, ZY)                                                 \
+    if (g.L1x == X1 && g.L2x == X2 && g.L1y == Y1 && g.L2y == Y2 && (g.zx & ZX) == ZX &&          \
+        (g.fx & FX) == FX && (g.zy & ZY) == ZY)                                                   \
+        return true;
+    VLOC_FULL_SPECS(VLOC_FULL_HAVE)
+#undef VLOC_FULL_HAVE
+    return (g.N1 == 96 || g.N1 == 72 || g.N1 == 128) && (g.N2 == 96 || g.N2 == 128);
+}
+
 template <typename T>
 hipError_t launch_plane(const Geometry &g, const LaneQuads &lq, const DevTables &t, const Launch &L, int mode, void *S,
                         const void *V, void *psi, int64_t band0, int threads, int lds_bytes,
@@ -2866,6 +2957,13 @@ hipError_t launch_plane(const Geometry &g, const LaneQuads &lq, const DevTables 
         if constexpr (std::is_same<T, double>::value &&
                       (M == MODE_APPLY || M == MODE_DENSITY || M == MODE_APPLY_DENSITY))
             if (lq.q) return launch_plane_lq_mode<M>(g, lq, t, L, S, V, band0, st);
+        if constexpr (M == MODE_APPLY || M == MODE_DENSITY || M == MODE_APPLY_DENSITY)
+            if (g.full == 1 && !full_spec(g)) {
+                bool hit = false;
+                const hipError_t e = launch_plane_xline<T, M>(g, t, L, S, V, band0, threads,
+                                                              lds_bytes, st, hit);
+                if (hit) return e;
+            }
         return g.full ? launch_plane_full_mode<T, M>(g, t, L, S, V, psi, band0, threads,
                                                      lds_bytes, st)
                       : launch_plane_rows_mode<T, M>(g, t, L, S, V, psi, band0, threads,

@@ -83,6 +83,10 @@ struct LaneQuads {
     int nxo;  // most occupied x-planes of any segment
     int cus;  // compute units of the device
     int planes; // planes per workgroup of the launch
+    int cls;    // class of the sphere's reach on the x axis (lq_mask), the same for every
+                // k of a batch: known zeros fold into the codelets, and that must not
+                // depend on the other members
+    int ynarrow; // reach on the y axis of at most 0.29 N2
     unsigned zm, lo, hi; // bit n: points 4 n .. 4 n + 3 unoccupied / occupied with
                          // x <= hmax / occupied with x >= N1 + hmin, for every segment
 };
@@ -217,6 +221,12 @@ inline LqLaunch lq_launch(const Geometry &g, const LaneQuads &lq, int mode, int6
     }
     return best;
 }
+// Whole-plane kernels with a compiled x split and the y split at run time; hit =
+// false where none applies.
+template <typename T, int MODE>
+hipError_t launch_plane_xline(const Geometry &g, const DevTables &t, const Launch &L, void *S,
+                              const void *VT, int64_t band0, int threads, int lds,
+                              hipStream_t st, bool &hit);
 // Compiled specialisations of the whole-plane application kernel for the
 // splits the schedule tuner tries; hit = false where none applies.
 template <typename T>

@@ -93,7 +93,9 @@ def test_lane_quads_vs_oracle_and_whole_plane(grid, R, k, nb):
     ((60, 64, 25), 10.0),
     ((80, 80, 30), 14.9),    # narrow sphere
     ((80, 80, 50), 24.9),    # some members within 0.315 of the axis, some not
-    ((100, 40, 40), 19.0),
+    ((100, 40, 40), 9.8),    # narrower than the compiled classes
+    ((64, 64, 60), 16.0),    # the quarter sphere: hmin and hmax differ between members
+    ((64, 64, 60), 19.9),    # near the limits of the wider class
     ((72, 96, 20), 9.0),
     ((96, 96, 50), 24.0),    # the quarter sphere, and shifted ones
 ])
@@ -102,7 +104,7 @@ def test_lane_quads_batch_equals_plans(grid, R):
     launches, band chunks that cut through them, and the plans' own results."""
     print("CASE", dict(test="lane_quads_batch", grid=grid), flush=True)
     cell, ecut = synth.cubic_cell(), synth.ecut_for_radius(R)
-    kpts = [(0, 0, 0), (0.25, 0.25, 0.25), (0.5, 0, 0), (0, 0.5, 0.25)]
+    kpts = [(0, 0, 0), (0.9, -0.7, 0.25), (0.5, 0, 0), (-0.6, 0.5, 0.25)]
     nbs = [3, 0, 5, 2]
     V = synth.potential(grid, 4)
     for chunk in (0, 4):
