@@ -39,7 +39,7 @@ def log(*a):
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("kernels.hip", "dft_codelets.h", "kernels.hpp"):
+    for f in ("kernels.hip", "plane_quads.hip", "kernel_common.h", "dft_codelets.h", "kernels.hpp"):
         with open(os.path.join(ROOT, "paper_1601_07378_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -474,7 +474,8 @@ def main():
                      "avg_launch_ms": round(k2_avg_s * 1e3, 4),
                      "timing": "per-launch HIP events on the plan stream, second timed region of "
                                "the same steps",
-                     "measured_limiter": "LDS traffic and VALU issue (SQ counters in profiles/)"},
+                     "measured_limiter": "VALU issue and waits on LDS and barriers (SQ counters in "
+                                         "profiles/)"},
         "kernel_ms_per_step": split,
         "schedule": r["schedule"],
         "schedule_source": r["schedule_source"],

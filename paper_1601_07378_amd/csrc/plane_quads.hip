@@ -21,15 +21,16 @@
 // writes and vector issue with little overlap.  Here the occupied columns are
 // the only x traffic (half the LDS bytes of a plane), only they live in LDS (two
 // 96 x 96 planes fit one CU, and a 128 x 128 plane fits without parts), and what
-// is left is vector issue (10.4k wave instructions per 96 x 96 plane, a lane swap
-// counting twice, 49% of the time) and waits: at four registers per point only
-// two or three waves fit a SIMD.  Runtime y sizes cost little, since the x pass,
+// is left is vector issue (10.5k wave instructions per 96 x 96 plane, a lane swap
+// taking two slots: 62% of a CU's busy cycles) and waits: at four registers per point
+// only two or three waves fit a SIMD.  Runtime y sizes cost little, since the x pass,
 // two thirds of the arithmetic, is compiled for every Q.
-// Whole applications, quarter sphere, rows in LDS -> lane quads: 32^3 x 3662
-// bands 2472 -> 858 us, 48^3 x 1085 1494 -> 827, 60^3 x 555 1289 -> 760, 64^3 x 457
-// 1116 -> 732, 72^3 x 321 1110 -> 999, 80^3 x 234 711 -> 661, 96^3 x 135 662 -> 632,
-// 100^3 x 120 1221 -> 1089, 120^3 x 69 1237 -> 980, 128^3 x 57 (parted plane) 1075 ->
-// 693; density 1.05-3.7 times, energy and gradients 0.97 (80^3) - 2.9 times.
+// Whole applications, quarter sphere, rows in LDS -> lane quads (with the other steps
+// of a call as they are now): 36^3 x 2572 bands 2204 -> 948 us, 48^3 x 1085 1496 -> 759,
+// 60^3 x 555 1289 -> 684, 64^3 x 457 1114 -> 689, 72^3 x 321 1112 -> 949, 80^3 x 1001
+// 3013 -> 2896, 96^3 x 256 1188 -> 1177, 100^3 x 120 1222 -> 1047, 120^3 x 69 1234 -> 932,
+// 128^3 x 96 (parted plane before) 1894 -> 1240; density 1.05 - 3.7 times, energy and
+// gradients 1.04 - 2.9 times.
 // FP32 planes are bound by vector issue at two workgroups per CU already and
 // gained nothing (96^3 x 256 bands 696 -> 699 us), so FP32 keeps rows in LDS.
 // Measured and left out: y stage B inside the row blocks' wavefronts (two
