@@ -197,14 +197,15 @@ inline int lq_lds_bytes(int q, int n2, int nxo, int planes)
 struct LqLaunch {
     int planes, threads, lds, resident;
 };
-inline LqLaunch lq_launch(const Geometry &g, const LaneQuads &lq, int mode, int64_t bands)
+inline LqLaunch lq_launch(const Geometry &g, const LaneQuads &lq, int mode, int64_t bands,
+                          int max_planes = 4)
 {
     const int wpe = lq_wpe(mode, lq.q, lq_ymax(g)), cap = 4 * wpe;
     const int blocks = (g.N2 + 15) / 16;
     LqLaunch best{};
     double least = 0.0;
     int most = 0; // wavefronts on a CU
-    for (int p = 1; p <= 4 && (p == 1 || p <= bands); ++p) {
+    for (int p = 1; p <= max_planes && (p == 1 || p <= bands); ++p) {
         const int lds = lq_lds_bytes(lq.q, g.N2, lq.nxo, p);
         const int units = p * blocks, rounds = (units + cap - 1) / cap;
         const int waves = (units + rounds - 1) / rounds;

@@ -595,6 +595,19 @@ constexpr unsigned lq_mask(int Q, int cls, int what)
     return m;
 }
 
+// Planes per workgroup whose offsets from the first one's slice of S, counted in
+// values, stay within 31 bits (a density workgroup's planes are a whole band subset
+// apart).
+template <int MODE>
+static int lq_max_planes(const Geometry &g, const Launch &L)
+{
+    long long nst = 0, step = 1;
+    for (int s = 0; s < L.nseg; ++s) nst = std::max<long long>(nst, L.seg[s].nst);
+    if (MODE != MODE_APPLY) step = (L.nbt + g.nsub - 1) / g.nsub;
+    const long long most = 0x7FFFFFFFLL / std::max(1LL, step * g.N3 * nst);
+    return (int)std::max(1LL, std::min(4LL, most));
+}
+
 template <int MODE, int Q, int CLS, int CY1, int CY2, int ZY, int YT, int MR>
 static hipError_t launch_lq_kernel(const Geometry &g, LaneQuads lq, const DevTables &t,
                                    const Launch &L, void *S, const void *VT, int64_t band0,
@@ -603,7 +616,8 @@ static hipError_t launch_lq_kernel(const Geometry &g, LaneQuads lq, const DevTab
     constexpr int WPE = lq_wpe(MODE, Q, MR), MAXT = 256 * WPE;
     auto kern = k_plane_lq<MODE, Q, lq_mask(Q, CLS, 0), lq_mask(Q, CLS, 1), lq_mask(Q, CLS, 2),
                            CY1, CY2, ZY, YT, MR, MAXT, WPE>;
-    const LqLaunch ll = lq_launch(g, lq, MODE, MODE == MODE_APPLY ? L.nbt : g.nsub);
+    const LqLaunch ll = lq_launch(g, lq, MODE, MODE == MODE_APPLY ? L.nbt : g.nsub,
+                                  lq_max_planes<MODE>(g, L));
     lq.planes = ll.planes;
     hipError_t e = allow_lds(kern, (size_t)ll.lds);
     if (e != hipSuccess) return e;
@@ -630,7 +644,8 @@ static hipError_t launch_lq_q(const Geometry &g, const LaneQuads &lq, const DevT
                (lq.lo & lq_mask(Q, cls, 1)) == lq_mask(Q, cls, 1) &&
                (lq.hi & lq_mask(Q, cls, 2)) == lq_mask(Q, cls, 2);
     };
-    const LqLaunch ll = lq_launch(g, lq, MODE, MODE == MODE_APPLY ? L.nbt : g.nsub);
+    const LqLaunch ll = lq_launch(g, lq, MODE, MODE == MODE_APPLY ? L.nbt : g.nsub,
+                                  lq_max_planes<MODE>(g, L));
     const int ytasks = (ll.planes * lq.nxo * g.L2y + ll.threads - 1) / ll.threads;
     // compiled y splits (their zero masks hold for a reach of up to 0.29 N2), then
     // runtime y sizes, which take class 1 for 2 as well
