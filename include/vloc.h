@@ -105,7 +105,11 @@ typedef struct {
     int32_t plane_xwaves;     /* wavefronts of the plane workgroup that run the x
                                  pass (each with its own row buffer); 0 = auto     */
     int32_t plane_xmode;      /* layout of the plane kernel: 0 = automatic (3 where
-                                 the whole plane fits in LDS, else 6, else 1); 1 = the
+                                 the whole plane fits in LDS, else 6, else 1; FP64
+                                 application and density then run the lane-quad
+                                 kernel where N1 / 4 is a codelet of 8 to 32 points,
+                                 unless plane_threads, plane_rows, plane_xwaves or an
+                                 x or y split is given as well); 1 = the
                                  occupied x-planes plus per-wavefront row buffers;
                                  2 = occupied x-planes, one lane quad per x row
                                  (needs N1 in {24, 72, 80, 96} with the matching y
