@@ -312,7 +312,9 @@ vloc_status vloc_r2g(vloc_plan plan, const void *psi_r, int64_t nbands, void *c_
  * With the whole-plane layouts (plane_xmode 3 and 4) each member keeps its own
  * occupied x-planes (each launch segment carries them); with the others each
  * member covers the union of the k-points' occupied x-planes.  Either way a
- * member plan's own results (vloc_batch_plan) equal its part of the batch. */
+ * member plan's own results (vloc_batch_plan) equal its part of the batch: to
+ * rounding, and bit for bit where no k-point reaches a part of an axis that the
+ * member's kernels are compiled to skip and the others' are not. */
 typedef struct vloc_batch_s *vloc_batch; /* opaque; owned by the library */
 
 /* nk in [1, 8]; kpts: nk*3 doubles (reduced coordinates, as for a plan).

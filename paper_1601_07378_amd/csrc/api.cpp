@@ -43,10 +43,13 @@ struct Engine {
     size_t S_bytes = 0;
     double *d_partial = nullptr; // density partial planes
     size_t partial_bytes = 0;
-    void *d_VT = nullptr;        // potential in the full-plane kernel's order
+    // potential in the plane kernel's order: the layout's own, the lane quads'
+    void *d_VT[2] = {nullptr, nullptr};
     void *d_parts = nullptr;     // parted plane: nxo x N2 values per resident workgroup
     Geometry geo{};
-    LaneQuads lq{};
+    // plane kernels of the members; members of one route share launches
+    std::vector<LaneQuads> routes;
+    std::vector<int> route_of; // per member
     // kernel timing: events[4*i .. 4*i+3] bracket K1, K2, K3 of launch i
     bool timing = false;
     std::vector<hipEvent_t> events;
@@ -126,7 +129,7 @@ void free_device(Engine &E)
     for (void *&t : E.d_tw) free_ptr(t);
     free_ptr(E.d_S);
     free_ptr(E.d_partial);
-    free_ptr(E.d_VT);
+    for (void *&v : E.d_VT) free_ptr(v);
     free_ptr(E.d_parts);
     E.partial_bytes = 0;
     E.S_bytes = 0;
@@ -174,56 +177,91 @@ hipError_t upload_vec(V *&dst, const std::vector<V> &src)
     return hipMemcpy(dst, src.data(), sizeof(V) * src.size(), hipMemcpyHostToDevice);
 }
 
-// Chooses the lane-quad plane kernel for the application and the density (the
-// diagnostic transforms keep the layout's own kernel) where the schedule is
-// automatic and the grid and the occupied x-planes of every member allow it.
-void set_lane_quads(Engine &E, int cus)
+// Lane-quad plane kernel of one plan (application and density; the diagnostic
+// transforms keep the layout's own kernel): taken where the schedule is automatic and
+// the grid and the sphere allow it.  What decides the arithmetic follows from the
+// sphere itself, not from a range it is laid out on, so that a batch member computes
+// what its own plan computes.
+LaneQuads plan_lane_quads(const HostPlan &m, const Geometry &g, int cus)
 {
-    const Geometry &g = E.geo;
-    const HostPlan &h = *E.members[0];
-    E.lq = LaneQuads{};
-    const vloc_options &o = h.opt;
-    if (o.precision != VLOC_F64 || (h.plane_full != 1 && h.plane_full != 4) || o.plane_xmode ||
+    const LaneQuads none{};
+    const vloc_options &o = m.opt;
+    if (o.precision != VLOC_F64 || (m.plane_full != 1 && m.plane_full != 4) || o.plane_xmode ||
         o.plane_threads || o.plane_rows || o.plane_xwaves || o.split[0] || o.split[1])
-        return;
-    if (std::max(g.L1y, g.L2y) > 16) return;
+        return none;
+    if (std::max(g.L1y, g.L2y) > 16) return none;
     LaneQuads lq{};
 #define VLOC_LQ_HAVE(Q)                                                                            \
     if (g.N1 == 4 * Q) lq.q = Q;
     VLOC_LQ_SIZES(VLOC_LQ_HAVE)
 #undef VLOC_LQ_HAVE
-    if (!lq.q) return;
+    if (!lq.q) return none;
     lq.cus = cus;
     lq.planes = 1;
-    // classes by the reach |h + k| <= ext of the sphere on the x and y axes, which the
-    // k-points of a batch share
-    auto reach = [&](int axis) {
-        const double *a = h.cell + 3 * axis;
-        return std::sqrt(2.0 * h.ecut * (a[0] * a[0] + a[1] * a[1] + a[2] * a[2])) /
-               6.283185307179586476925;
-    };
-    const double ex = reach(0), ey = reach(1), tol = 1e-9 * g.N1;
-    lq.cls = ex >= g.N1 / 4.0 - 1.0 && ex <= g.N1 / 4.0 + tol ? 2
-             : ex >= 0.19 * g.N1 && ex <= 0.32 * g.N1         ? 1
-                                                              : 0;
-    lq.ynarrow = ey <= 0.29 * g.N2;
-    lq.zm = lq.lo = lq.hi = ~0u;
-    for (const HostPlan *m : E.members) {
-        // the kernel takes x >= N1 + hmin as one occupied range and 0 <= x <= hmax
-        // as the other, and keeps slots in 16 bits
-        if (m->hmin >= 0 || m->hmax < 0 || m->nst() >= 0xFFFF) return;
-        if (std::abs(m->kpt[0]) > 1.0) lq.cls = 0;
-        if (std::abs(m->kpt[1]) > 1.0) lq.ynarrow = 0;
-        lq.nxo = std::max(lq.nxo, (int)m->nxo);
-        for (int n = 0; n < lq.q; ++n) {
-            const int a = 4 * n, b = 4 * n + 3, hx = g.N1 + m->hmin; // points a .. b
-            if (!(a > m->hmax && b < hx)) lq.zm &= ~(1u << n);
-            if (!(b <= m->hmax)) lq.lo &= ~(1u << n);
-            if (!(a >= hx)) lq.hi &= ~(1u << n);
-        }
+    lq.nxo = m.nxo;
+    if (m.nst() >= 0xFFFF || lq_lds_bytes(lq.q, g.N2, lq.nxo, 1) > 160 * 1024) return none;
+    int hlo = m.sticks[0].h, hhi = hlo, klo = m.sticks[0].k, khi = klo;
+    for (const Stick &s : m.sticks) {
+        hlo = std::min(hlo, s.h);
+        hhi = std::max(hhi, s.h);
+        klo = std::min(klo, s.k);
+        khi = std::max(khi, s.k);
     }
-    if (lq_lds_bytes(lq.q, g.N2, lq.nxo, 1) > 160 * 1024) return;
-    E.lq = lq;
+    // the kernel takes x >= N1 + hmin as one occupied range and 0 <= x <= hmax as the
+    // other, and keeps slots in 16 bits
+    if (hlo >= 0 || hhi < 0) return none;
+    unsigned in[3] = {0, 0, 0}; // points a .. b empty, low and high, as in lq_mask
+    for (int n = 0; n < lq.q; ++n) {
+        const int a = 4 * n, b = 4 * n + 3;
+        if (a > hhi && b < g.N1 + hlo) in[0] |= 1u << n;
+        if (b <= hhi) in[1] |= 1u << n;
+        if (a >= g.N1 + hlo) in[2] |= 1u << n;
+    }
+    auto fits = [&](int cls) {
+        for (int w = 0; w < 3; ++w)
+            if ((in[w] & lq_mask(lq.q, cls, w)) != lq_mask(lq.q, cls, w)) return false;
+        return true;
+    };
+    // class by the sphere's reach |h + k| <= ext on the x axis, where its masks hold
+    const double *a1 = m.cell;
+    const double ext = std::sqrt(2.0 * m.ecut * (a1[0] * a1[0] + a1[1] * a1[1] + a1[2] * a1[2])) /
+                       6.283185307179586476925;
+    const bool quarter = ext >= g.N1 / 4.0 - 1.0 && ext <= g.N1 / 4.0 + 1e-9 * g.N1;
+    const bool middle = ext >= 0.19 * g.N1 && ext <= 0.32 * g.N1;
+    const int wide = !quarter && !middle ? 0 : fits(1) ? 1 : fits(4) ? 4 : 0;
+    lq.cls = quarter && fits(2) ? 2 : quarter && fits(3) ? 3 : wide;
+    // the compiled y split, if its rows are empty (for a centred sphere, a reach of up to
+    // a quarter of the axis); runtime y sizes take the wide classes
+    const Split sy{g.N2, g.L1y, g.L2y};
+    const int tasks = 2 * 64 * ((g.N2 + 15) / 16);
+#define VLOC_LQ_HAVE(Q, Y1, Y2, ZY)                                                                \
+    if (lq.cls && lq.q == Q && sy.L1 == Y1 && sy.L2 == Y2 && lq.nxo * Y2 <= tasks &&               \
+        (zero_mask(sy, klo, khi) & ZY) == ZY)                                                     \
+        lq.ysplit = 1;
+    VLOC_LQ_YSPLITS(VLOC_LQ_HAVE)
+#undef VLOC_LQ_HAVE
+    if (!lq.ysplit) lq.cls = wide;
+    return lq;
+}
+
+// The members' routes: members whose kernels differ get launches of their own kind.
+void set_routes(Engine &E, int cus)
+{
+    E.routes.clear();
+    E.route_of.clear();
+    for (const HostPlan *m : E.members) {
+        const LaneQuads lq = plan_lane_quads(*m, E.geo, cus);
+        size_t r = 0;
+        while (r < E.routes.size() && (E.routes[r].q != lq.q || E.routes[r].cls != lq.cls ||
+                                       E.routes[r].ysplit != lq.ysplit))
+            ++r;
+        if (r == E.routes.size()) {
+            E.routes.push_back(lq);
+        } else {
+            E.routes[r].nxo = std::max(E.routes[r].nxo, lq.nxo);
+        }
+        E.route_of.push_back((int)r);
+    }
 }
 
 vloc_status upload(Engine &E)
@@ -313,10 +351,6 @@ vloc_status upload(Engine &E)
     if (!gam.empty() && (e = upload_vec(E.d_gam, gam)) != hipSuccess) goto devfail;
     if (!yslot.empty() && (e = upload_vec(E.d_yslot, yslot)) != hipSuccess) goto devfail;
     if (!holes.empty() && (e = upload_vec(E.d_holes, holes)) != hipSuccess) goto devfail;
-    if (h.plane_full) {
-        const size_t vbytes = (size_t)h.grid[0] * h.grid[1] * h.grid[2] * (h.elem_bytes() / 2);
-        if ((e = hipMalloc(&E.d_VT, vbytes)) != hipSuccess) goto devfail;
-    }
     {
         const Split *sp[3] = {&h.sx, &h.sy, &h.sz};
         for (int a = 0; a < 3; ++a) {
@@ -398,7 +432,14 @@ vloc_status upload(Engine &E)
         const int lt = plane_launch_threads(g, h.plane_threads);
         if (lt < h.plane_threads) per_cu = std::max(per_cu, std::min(fit, 1024 / lt));
         g.resident_plane_wgs = cus * per_cu;
-        set_lane_quads(E, cus);
+        set_routes(E, cus);
+        if (h.plane_full) {
+            const size_t vbytes = (size_t)g.N1 * g.N2 * g.N3 * (h.elem_bytes() / 2);
+            for (const LaneQuads &lq : E.routes) {
+                void *&vt = E.d_VT[lq.q != 0];
+                if (!vt && (e = hipMalloc(&vt, vbytes)) != hipSuccess) goto devfail;
+            }
+        }
         if (h.plane_full == 4) {
             // one scratch region per workgroup of the persistent plane grid
             const size_t pb = (size_t)g.resident_plane_wgs * h.nxo * h.grid[1] * h.elem_bytes();
@@ -524,8 +565,8 @@ void fill_seg(const Engine &E, int member, const void *in, void *out, int64_t nb
 // chunks of at most `chunk`), and only the smaller members share launches: a
 // launch of one segment runs the plane kernel's direct y form, and a member
 // that large fills the device by itself.  In the real mode a launch band is a
-// pair of the caller's bands.  Returns the stick-buffer bytes of the largest
-// chunk.
+// pair of the caller's bands.  Members of different routes never share a launch.
+// Returns the stick-buffer bytes of the largest chunk.
 size_t make_launches(const Engine &E, const void *const *in, void *const *out,
                      const int64_t *nbands, int64_t chunk, std::vector<Launch> &ls,
                      int64_t own = 0, int64_t own_cap = 0)
@@ -554,6 +595,7 @@ size_t make_launches(const Engine &E, const void *const *in, void *const *out,
         }
         L.nbt = band_lo;
         L.nblk = blk_lo;
+        L.route = E.route_of[cur[0].member];
         need = std::max(need, (size_t)s_off * (size_t)E.members[0]->elem_bytes());
         ls.push_back(L);
         cur.clear();
@@ -562,7 +604,10 @@ size_t make_launches(const Engine &E, const void *const *in, void *const *out,
         emit(cur);
         cur_bands = 0;
     };
-    for (int m = 0; m < nm; ++m) {
+    for (int i = 0; i < nm * (int)E.routes.size(); ++i) { // route by route
+        const int m = i % nm;
+        if (m == 0) flush();
+        if (E.route_of[m] != i / nm) continue;
         const int64_t units = E.members[m]->gamma ? (nbands[m] + 1) / 2 : nbands[m];
         if (own > 0 && units >= own) {
             const int64_t nch = (units + own_cap - 1) / own_cap;
@@ -592,7 +637,7 @@ size_t make_launches(const Engine &E, const void *const *in, void *const *out,
 template <typename T>
 vloc_status run_launches(Engine &E, int mode, const Launch *ls, size_t nl, const void *V,
                          void *psi, const double *wts, hipStream_t st, bool timed, void *S,
-                         void *VT, bool arrange = true)
+                         void *const VT[2], bool arrange = true)
 {
     const HostPlan &h = *E.members[0];
     const Geometry &g = E.geo;
@@ -600,15 +645,14 @@ vloc_status run_launches(Engine &E, int mode, const Launch *ls, size_t nl, const
     t.wts = wts;
     hipError_t e;
     int64_t band0 = 0;
-    // the potential in the plane kernel's order, once per call, by the first stick
-    // launch (with arrange false, VT already holds it)
-    const void *Va = nullptr;
-    if ((mode == MODE_APPLY || mode == MODE_APPLY_DENSITY) && g.full) {
-        if (arrange) Va = V;
-        V = VT;
-    }
+    // the potential in the plane kernel's order, once per call and order, by the first
+    // stick launch that needs it (with arrange false, VT already holds it)
+    const bool ordered = (mode == MODE_APPLY || mode == MODE_APPLY_DENSITY) && g.full;
+    bool have[2] = {!arrange, !arrange};
     for (size_t li = 0; li < nl; ++li) {
         const Launch &L = ls[li];
+        const LaneQuads &lq = E.routes[L.route];
+        void *vt = VT[lq.q != 0];
         hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
         if (timed) {
             if ((e = next_events(E, ev)) != hipSuccess) return hip_fail(e, "hipEventCreate");
@@ -616,12 +660,14 @@ vloc_status run_launches(Engine &E, int mode, const Launch *ls, size_t nl, const
             (void)hipEventRecord(ev[0], st);
         }
         if (mode != MODE_R2G) {
-            e = launch_stick_fwd<T>(g, E.lq, t, L, S, li == 0 ? Va : nullptr, VT, h.stick_threads,
-                                    st);
+            const bool now = ordered && !have[lq.q != 0];
+            e = launch_stick_fwd<T>(g, lq, t, L, S, now ? V : nullptr, vt, h.stick_threads, st);
+            if (now) have[lq.q != 0] = true;
             if (e != hipSuccess) return hip_fail(e, "stick forward launch");
         }
         if (timed) (void)hipEventRecord(ev[1], st);
-        e = launch_plane<T>(g, E.lq, t, L, mode, S, V, psi, band0, h.plane_threads, plane_lds(E), st);
+        e = launch_plane<T>(g, lq, t, L, mode, S, ordered ? vt : V, psi, band0, h.plane_threads,
+                            plane_lds(E), st);
         if (e != hipSuccess) return hip_fail(e, "plane launch");
         if (timed) (void)hipEventRecord(ev[2], st);
         if (mode != MODE_G2R && mode != MODE_DENSITY) {
@@ -821,7 +867,7 @@ vloc_status vloc_apply_noalloc(vloc_plan plan, const void *c, int64_t nbands, co
     void *base = nullptr;
     vloc_status s = scratch_address(dev, &base);
     if (s != VLOC_OK) return s;
-    void *VT = base;
+    void *const VT[2] = {base, base};
     void *S = static_cast<char *>(base) + vt;
     // equal chunks of at most this many launch bands, as vloc_apply cuts them
     const int64_t cap = std::min<int64_t>(h.band_chunk, (int64_t)((kScratchBytes - vt) / per_band));
@@ -836,6 +882,7 @@ vloc_status vloc_apply_noalloc(vloc_plan plan, const void *c, int64_t nbands, co
         fill_seg(E, 0, c, out, nbands, b0, nb, 0, 0, 0, L.seg[0]);
         L.nbt = nb;
         L.nblk = nb * h.ngroups;
+        L.route = 0;
         // the first chunk arranges the potential into VT (whole-plane layout);
         // the later ones read it from there
         s = f32 ? run_launches<float>(E, MODE_APPLY, &L, 1, V, nullptr, nullptr, E.stream, false,
@@ -944,8 +991,8 @@ namespace {
 // `bands` bands.
 int density_planes(const Engine &E, int mode, int64_t bands)
 {
-    if (!E.lq.q) return E.geo.resident_plane_wgs;
-    const LqLaunch l = lq_launch(E.geo, E.lq, mode, bands);
+    if (!E.routes[0].q) return E.geo.resident_plane_wgs;
+    const LqLaunch l = lq_launch(E.geo, E.routes[0], mode, bands);
     return l.resident * l.planes;
 }
 
@@ -1007,7 +1054,7 @@ vloc_status density_pass(vloc_plan plan, int mode, const void *c, int64_t nbands
     if (e != hipSuccess) return hip_fail(e, "fill launch");
     s = dispatch(plan, mode, c, nbands, V, out, w, dchunk);
     if (s != VLOC_OK) return s;
-    e = launch_density_reduce(g, E.lq, E.d_partial, g.nsub, scale, rho, E.stream);
+    e = launch_density_reduce(g, E.routes[0], E.d_partial, g.nsub, scale, rho, E.stream);
     return e == hipSuccess ? VLOC_OK : hip_fail(e, "density reduce launch");
 }
 

@@ -76,19 +76,18 @@ inline int plane_launch_threads(const Geometry &g, int threads)
     return std::min(threads, std::max(256, (tasks + 255) / 256 * 256));
 }
 
-// Lane-quad plane kernel of a plan (application and density; q = 0: the
-// layout's own kernel runs them).
+// Lane-quad plane kernel (application and density; q = 0: the layout's own kernel
+// runs them) of the plans that share a route.  Known zeros, and tests in the place of
+// loads known to be needed, change which products the compiler fuses, so q, cls and
+// ysplit decide the last bits of a result: they follow from a plan's own sphere, and
+// only plans that agree in them share launches.
 struct LaneQuads {
     int q;    // x axis of 4 q points
-    int nxo;  // most occupied x-planes of any segment
+    int nxo;  // most occupied x-planes of any plan
     int cus;  // compute units of the device
     int planes; // planes per workgroup of the launch
-    int cls;    // class of the sphere's reach on the x axis (lq_mask), the same for every
-                // k of a batch: known zeros fold into the codelets, and that must not
-                // depend on the other members
-    int ynarrow; // reach on the y axis of at most 0.29 N2
-    unsigned zm, lo, hi; // bit n: points 4 n .. 4 n + 3 unoccupied / occupied with
-                         // x <= hmax / occupied with x >= N1 + hmin, for every segment
+    int cls;    // class of occupied and empty x points (lq_mask)
+    int ysplit; // the y split compiled with its zero mask (VLOC_LQ_YSPLITS)
 };
 
 // One launch covers the bands of up to kMaxSeg k-points ("segments") that
@@ -117,6 +116,7 @@ struct Launch {
     int nbt;   // bands of all segments
     int nblk;  // stick-kernel blocks of all segments
     Seg seg[kMaxSeg];
+    int route; // the segments' route (host only)
 };
 
 // Arrangement of the potential in the plane kernel's order, next to K1's work.
@@ -161,6 +161,28 @@ hipError_t launch_plane_lq_mode(const Geometry &g, const LaneQuads &lq, const De
 // Register codelets Q of the lane-quad kernel (x axis of 4 Q points).
 #define VLOC_LQ_SIZES(X)                                                                           \
     X(8) X(9) X(10) X(12) X(15) X(16) X(18) X(20) X(24) X(25) X(27) X(30) X(32)
+// Compiled y splits {Q, L1y, L2y, zero mask}, for at most two stage-A tasks per thread.
+#define VLOC_LQ_YSPLITS(X)                                                                         \
+    X(24, 8, 12, 0x38) X(18, 8, 12, 0x38) X(32, 16, 8, 0xFE0) X(20, 8, 10, 0x38)
+// Masks of a class of spheres (LaneQuads::cls), bit n for the points 4 n .. 4 n + 3:
+// 2 = for a reach ext on the x axis from N1/4 - 1 to N1/4 (the grid that holds V psi
+// exactly), 1 = from 0.19 to 0.32 N1, 0 = any.  `what`: 0 = points left empty, for every
+// k-point with |h + k| <= ext and |k| <= 1; 1 / 2 = points occupied with x <= hmax / x >=
+// N1 + hmin, for most k (classes 3 and 4 are 2 and 1 without them).
+constexpr unsigned lq_mask(int Q, int cls, int what)
+{
+    const int N = 4 * Q;
+    const bool quarter = cls == 2 || cls == 3;
+    const int in = quarter ? N / 4 - 1 : (int)(0.18 * N);
+    const int out = quarter ? N / 4 + 1 : (int)(0.32 * N) + 1;
+    unsigned m = 0;
+    for (int n = 0; n < Q && cls && (what == 0 || cls < 3); ++n) {
+        const int a = 4 * n, b = 4 * n + 3;
+        const bool on = what == 0 ? (a > out && b < N - out) : what == 1 ? b <= in : a >= N - in;
+        if (on) m |= 1u << n;
+    }
+    return m;
+}
 // Waves per SIMD the kernel is compiled for: a lane holds four registers per
 // point of its Q, and in the density alone two more for the sums; y codelets of
 // 15 and 16 points need more than the 128 registers that four waves leave.

@@ -83,9 +83,7 @@ std::vector<double> twiddle_table(int L)
     return t;
 }
 
-// Bit n1 is set when no occupied position v in [lo, hi] (taken mod L) falls in
-// the stage-A input group {n2 + L2 n1 : n2 < L2}.
-static int32_t zero_mask(const Split &s, long lo, long hi)
+int32_t zero_mask(const Split &s, long lo, long hi)
 {
     int32_t m = 0;
     for (int n1 = 0; n1 < s.L1; ++n1) {

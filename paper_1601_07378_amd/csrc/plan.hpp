@@ -85,6 +85,9 @@ vloc_status build_host_plan(HostPlan &p, const int32_t grid[3], const double cel
                             const Occupied *cover = nullptr);
 
 bool split_length(int L, Split &s);
+// Bit n1 is set when no occupied position v in [lo, hi] (taken mod L) falls in
+// the stage-A input group {n2 + L2 n1 : n2 < L2}.
+int32_t zero_mask(const Split &s, long lo, long hi);
 bool is_codelet(int r); // r is a compiled codelet length
 
 // exp(-2 pi i j / L) for j < L, FP64, angle numerator reduced exactly.

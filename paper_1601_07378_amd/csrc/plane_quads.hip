@@ -574,26 +574,6 @@ void k_plane_lq(Geometry g, LaneQuads lq, DevTables t, Launch L, double2 *__rest
 }
 
 // ------------------------------------------------------------- launcher
-//
-// Masks of a class of spheres (LaneQuads::cls) by their reach ext on the x axis (|h + k|
-// <= ext, |k| <= 1): 2 = ext from N1/4 - 1 to N1/4 (the grid that holds V psi exactly),
-// 1 = from 0.19 to 0.32 N1, 0 = any.  `what`: 0 = points left empty, for every k of the
-// class; 1 / 2 = points occupied with x <= hmax / x >= N1 + hmin, for most k (classes 3
-// and 4 are 2 and 1 without them: the same arithmetic, more tests).
-constexpr unsigned lq_mask(int Q, int cls, int what)
-{
-    const int N = 4 * Q;
-    const bool quarter = cls == 2 || cls == 3;
-    const int in = quarter ? N / 4 - 1 : (int)(0.18 * N);
-    const int out = quarter ? N / 4 + 1 : (int)(0.32 * N) + 1;
-    unsigned m = 0;
-    for (int n = 0; n < Q && cls && (what == 0 || cls < 3); ++n) {
-        const int a = 4 * n, b = 4 * n + 3;
-        const bool on = what == 0 ? (a > out && b < N - out) : what == 1 ? b <= in : a >= N - in;
-        if (on) m |= 1u << n;
-    }
-    return m;
-}
 
 // Planes per workgroup whose offsets from the first one's slice of S, counted in
 // values, stay within 31 bits (a density workgroup's planes are a whole band subset
@@ -639,46 +619,35 @@ static hipError_t launch_lq_q(const Geometry &g, const LaneQuads &lq, const DevT
                               const Launch &L, void *S, const void *VT, int64_t band0,
                               hipStream_t st)
 {
-    auto fits = [&](int cls) {
-        return (lq.zm & lq_mask(Q, cls, 0)) == lq_mask(Q, cls, 0) &&
-               (lq.lo & lq_mask(Q, cls, 1)) == lq_mask(Q, cls, 1) &&
-               (lq.hi & lq_mask(Q, cls, 2)) == lq_mask(Q, cls, 2);
-    };
-    const LqLaunch ll = lq_launch(g, lq, MODE, MODE == MODE_APPLY ? L.nbt : g.nsub,
-                                  lq_max_planes<MODE>(g, L));
-    const int ytasks = (ll.planes * lq.nxo * g.L2y + ll.threads - 1) / ll.threads;
-    // compiled y splits (their zero masks hold for a reach of up to 0.29 N2), then
-    // runtime y sizes, which take class 1 for 2 as well
+    // the compiled y splits, where the plans' rows leave the zero mask empty
 #define VLOC_LQ_YC(C, Y1, Y2, ZY)                                                                  \
-    if (fits(C))                                                                                  \
+    if (lq.cls == C)                                                                              \
         return launch_lq_kernel<MODE, Q, C, Y1, Y2, ZY, 2, 16>(g, lq, t, L, S, VT, band0, st);
 #define VLOC_LQ_Y(QQ, Y1, Y2, ZY)                                                                  \
     if constexpr (Q == QQ)                                                                         \
-        if (g.L1y == Y1 && g.L2y == Y2 && lq.ynarrow && (g.zy & ZY) == ZY && ytasks <= 2) {       \
-            if (lq.cls == 2) {                                                                    \
-                VLOC_LQ_YC(2, Y1, Y2, ZY)                                                         \
-                VLOC_LQ_YC(3, Y1, Y2, ZY)                                                         \
-            }                                                                                     \
-            if (lq.cls == 1) {                                                                    \
-                VLOC_LQ_YC(1, Y1, Y2, ZY)                                                         \
-                VLOC_LQ_YC(4, Y1, Y2, ZY)                                                         \
-            }                                                                                     \
+        if (lq.ysplit && g.L1y == Y1 && g.L2y == Y2) {                                            \
+            VLOC_LQ_YC(1, Y1, Y2, ZY)                                                             \
+            VLOC_LQ_YC(2, Y1, Y2, ZY)                                                             \
+            VLOC_LQ_YC(3, Y1, Y2, ZY)                                                             \
+            VLOC_LQ_YC(4, Y1, Y2, ZY)                                                             \
+            return hipErrorInvalidValue;                                                          \
         }
-    VLOC_LQ_Y(24, 8, 12, 0x38)
-    VLOC_LQ_Y(18, 8, 12, 0x38)
-    VLOC_LQ_Y(32, 16, 8, 0xFE0)
-    VLOC_LQ_Y(20, 8, 10, 0x38)
+    VLOC_LQ_YSPLITS(VLOC_LQ_Y)
 #undef VLOC_LQ_Y
 #undef VLOC_LQ_YC
+    // runtime y sizes
     auto sized = [&](auto cls) {
         constexpr int C = decltype(cls)::value;
         return lq_ymax(g) <= 12
                    ? launch_lq_kernel<MODE, Q, C, 0, 0, 0, 0, 12>(g, lq, t, L, S, VT, band0, st)
                    : launch_lq_kernel<MODE, Q, C, 0, 0, 0, 0, 16>(g, lq, t, L, S, VT, band0, st);
     };
-    if (lq.cls && fits(1)) return sized(std::integral_constant<int, 1>{});
-    if (lq.cls && fits(4)) return sized(std::integral_constant<int, 4>{});
-    return sized(std::integral_constant<int, 0>{});
+    switch (lq.cls) {
+    case 0: return sized(std::integral_constant<int, 0>{});
+    case 1: return sized(std::integral_constant<int, 1>{});
+    case 4: return sized(std::integral_constant<int, 4>{});
+    default: return hipErrorInvalidValue;
+    }
 }
 
 template <int MODE>
