@@ -230,6 +230,7 @@ LaneQuads plan_lane_quads(const HostPlan &m, const Geometry &g, int cus)
     const bool middle = ext >= 0.19 * g.N1 && ext <= 0.32 * g.N1;
     const int wide = !quarter && !middle ? 0 : fits(1) ? 1 : fits(4) ? 4 : 0;
     lq.cls = quarter && fits(2) ? 2 : quarter && fits(3) ? 3 : wide;
+    if (!lq_pays(g, lq, ext)) return none;
     // the compiled y split, if its rows are empty (for a centred sphere, a reach of up to
     // a quarter of the axis); runtime y sizes take the wide classes
     const Split sy{g.N2, g.L1y, g.L2y};

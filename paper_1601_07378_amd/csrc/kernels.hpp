@@ -244,6 +244,32 @@ inline LqLaunch lq_launch(const Geometry &g, const LaneQuads &lq, int mode, int6
     }
     return best;
 }
+// Is the lane-quad kernel faster than the layout's own, for a sphere of reach ext on
+// the x axis?  The layout's own kernels come with codelets of at most 12 points, or
+// with those of 15 and 16 too, which spill; the parted plane goes through a device
+// scratch.  Without masks of occupied points (class 0) every point of a row is tested,
+// and from Q = 15 on the lane quads spill as well (56 registers per lane; 130 and more
+// at Q = 24 to 27).  Whole calls on the layout's kernel -> on lane quads, FP64 (many
+// bands; a ratio where they are faster):
+//   reach 0.40 of each axis: 80^3 x 78 bands 517 -> 915 us, 96 x 72 x 96 x 60 546 -> 1093,
+//     64^3 x 152 547 -> 718, 128 x 64 x 128 x 38 723 -> 973; but 48^3 0.74 of the time,
+//     and with y codelets of 15 points 64 x 150 x 64 0.90, 72 x 135 x 64 0.73;
+//   reach 0.12: 96 x 72 x 96 257 -> 344, 108 x 90 x 64 233 -> 328, 120 x 80 x 64 239 ->
+//     309; but 80^3 0.91, 64^3 0.60, 96 x 32 x 64 0.70, 128^2 x 16 0.79, 120^2 x 64 0.90.
+// With masks, two waves per SIMD want workgroups that fill them: 120 x 80 x 64 x 65 bands,
+// reach 0.25, five waves on a CU, 1.13 times the time.
+inline bool lq_pays(const Geometry &g, const LaneQuads &lq, double ext)
+{
+    const int codelet = std::max(std::max(g.L1x, g.L2x), std::max(g.L1y, g.L2y));
+    const bool slow = g.full == 4 || codelet > 12; // the layout's own kernel
+    if (lq.cls) {
+        const LqLaunch l = lq_launch(g, lq, MODE_APPLY, 4);
+        const int waves = l.threads / 64 * std::max(1, l.resident / std::max(1, lq.cus));
+        return slow || lq_wpe(MODE_APPLY, lq.q, lq_ymax(g)) > 2 || 3 * waves > 16;
+    }
+    if (ext < 0.25 * g.N1) return lq.q <= 20 || slow || g.N2 <= 32;
+    return lq.q <= 12 || (lq.q <= 18 && codelet > 12);
+}
 // Whole-plane kernels with a compiled x split and the y split at run time; hit =
 // false where none applies.
 template <typename T, int MODE>
