@@ -218,8 +218,11 @@ hipError_t launch_density_reduce(const Geometry &g, const LaneQuads &lq, const d
     const int64_t n = (int64_t)g.N1 * g.N2 * g.N3;
     if (n <= 0) return hipSuccess;
     if (g.full) {
-        // at most 64 KiB of LDS
-        const int ty = g.N1 <= 480 ? 16 : 4;
+        // rows per workgroup: at most 64 KiB of LDS, and two workgroups per CU (each
+        // thread sums all subsets of its points in a serial chain: with 16 rows 24^3 had
+        // 48 workgroups and the FP32 density of 256 bands went from 60 to 79 us)
+        int ty = g.N1 <= 480 ? 16 : 4;
+        while (ty > 1 && (int64_t)g.N3 * ((g.N2 + ty - 1) / ty) < 512) ty /= 2;
         hipLaunchKernelGGL(k_density_reduce_rows, dim3((unsigned)(g.N3 * ((g.N2 + ty - 1) / ty))),
                            dim3(256), (size_t)g.N1 * (ty + 1) * sizeof(double), st, partial, nsub,
                            g.N1, g.N2, g.N3, ty, lq.q, g.L1y, g.L2y, g.inv_n, scale, rho);
