@@ -50,6 +50,7 @@ struct Engine {
     // plane kernels of the members; members of one route share launches
     std::vector<LaneQuads> routes;
     std::vector<int> route_of; // per member
+    LaneQuads dens{};          // of the density alone (first member)
     // kernel timing: events[4*i .. 4*i+3] bracket K1, K2, K3 of launch i
     bool timing = false;
     std::vector<hipEvent_t> events;
@@ -182,7 +183,7 @@ hipError_t upload_vec(V *&dst, const std::vector<V> &src)
 // the grid and the sphere allow it.  What decides the arithmetic follows from the
 // sphere itself, not from a range it is laid out on, so that a batch member computes
 // what its own plan computes.
-LaneQuads plan_lane_quads(const HostPlan &m, const Geometry &g, int cus)
+LaneQuads plan_lane_quads(const HostPlan &m, const Geometry &g, int cus, int mode)
 {
     const LaneQuads none{};
     const vloc_options &o = m.opt;
@@ -230,7 +231,7 @@ LaneQuads plan_lane_quads(const HostPlan &m, const Geometry &g, int cus)
     const bool middle = ext >= 0.19 * g.N1 && ext <= 0.32 * g.N1;
     const int wide = !quarter && !middle ? 0 : fits(1) ? 1 : fits(4) ? 4 : 0;
     lq.cls = quarter && fits(2) ? 2 : quarter && fits(3) ? 3 : wide;
-    if (!lq_pays(g, lq, ext)) return none;
+    if (!lq_pays(g, lq, ext, mode)) return none;
     // the compiled y split, if its rows are empty (for a centred sphere, a reach of up to
     // a quarter of the axis); runtime y sizes take the wide classes
     const Split sy{g.N2, g.L1y, g.L2y};
@@ -250,8 +251,9 @@ void set_routes(Engine &E, int cus)
 {
     E.routes.clear();
     E.route_of.clear();
+    E.dens = plan_lane_quads(*E.members[0], E.geo, cus, MODE_DENSITY);
     for (const HostPlan *m : E.members) {
-        const LaneQuads lq = plan_lane_quads(*m, E.geo, cus);
+        const LaneQuads lq = plan_lane_quads(*m, E.geo, cus, MODE_APPLY);
         size_t r = 0;
         while (r < E.routes.size() && (E.routes[r].q != lq.q || E.routes[r].cls != lq.cls ||
                                        E.routes[r].ysplit != lq.ysplit))
@@ -652,7 +654,7 @@ vloc_status run_launches(Engine &E, int mode, const Launch *ls, size_t nl, const
     bool have[2] = {!arrange, !arrange};
     for (size_t li = 0; li < nl; ++li) {
         const Launch &L = ls[li];
-        const LaneQuads &lq = E.routes[L.route];
+        const LaneQuads &lq = mode == MODE_DENSITY ? E.dens : E.routes[L.route];
         void *vt = VT[lq.q != 0];
         hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
         if (timed) {
@@ -990,10 +992,10 @@ namespace {
 
 // Planes that the device's workgroups hold at once in a density pass over
 // `bands` bands.
-int density_planes(const Engine &E, int mode, int64_t bands)
+int density_planes(const Engine &E, const LaneQuads &lq, int mode, int64_t bands)
 {
-    if (!E.routes[0].q) return E.geo.resident_plane_wgs;
-    const LqLaunch l = lq_launch(E.geo, E.routes[0], mode, bands);
+    if (!lq.q) return E.geo.resident_plane_wgs;
+    const LqLaunch l = lq_launch(E.geo, lq, mode, bands);
     return l.resident * l.planes;
 }
 
@@ -1013,6 +1015,7 @@ vloc_status density_pass(vloc_plan plan, int mode, const void *c, int64_t nbands
     const int64_t N = (int64_t)h.grid[0] * h.grid[1] * h.grid[2];
     const int64_t dchunk = h.density_chunk > 0 ? h.density_chunk : h.band_chunk;
     const int64_t chunk = nbands < dchunk ? nbands : dchunk;
+    const LaneQuads &lq = mode == MODE_DENSITY ? E.dens : E.routes[0];
     // band subsets per launch: items N3 * nsub fill the resident workgroups in
     // whole rounds where possible (fewest idle slots, then fewest subsets), among at
     // most two rounds' worth: every subset has a partial plane per z, which is
@@ -1020,7 +1023,7 @@ vloc_status density_pass(vloc_plan plan, int mode, const void *c, int64_t nbands
     // with up to four rounds' worth -> two: 80^3 x 234 FP64 1276 -> 978 us, 96^3 x 135
     // FP32 837 -> 757 us; with one, idle slots cost more: 1397 and 891 us)
     {
-        const int R = std::max(1, density_planes(E, mode, chunk));
+        const int R = std::max(1, density_planes(E, lq, mode, chunk));
         const int lo = std::max(1, (R + h.grid[2] - 1) / h.grid[2]);
         int best = lo;
         double best_w = 2.0;
@@ -1055,7 +1058,7 @@ vloc_status density_pass(vloc_plan plan, int mode, const void *c, int64_t nbands
     if (e != hipSuccess) return hip_fail(e, "fill launch");
     s = dispatch(plan, mode, c, nbands, V, out, w, dchunk);
     if (s != VLOC_OK) return s;
-    e = launch_density_reduce(g, E.routes[0], E.d_partial, g.nsub, scale, rho, E.stream);
+    e = launch_density_reduce(g, lq, E.d_partial, g.nsub, scale, rho, E.stream);
     return e == hipSuccess ? VLOC_OK : hip_fail(e, "density reduce launch");
 }
 

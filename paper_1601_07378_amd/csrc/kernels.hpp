@@ -248,27 +248,34 @@ inline LqLaunch lq_launch(const Geometry &g, const LaneQuads &lq, int mode, int6
 // the x axis?  The layout's own kernels come with codelets of at most 12 points, or
 // with those of 15 and 16 too, which spill; the parted plane goes through a device
 // scratch.  Without masks of occupied points (class 0) every point of a row is tested,
-// and from Q = 15 on the lane quads spill as well (56 registers per lane; 130 and more
-// at Q = 24 to 27).  Whole calls on the layout's kernel -> on lane quads, FP64 (many
-// bands; a ratio where they are faster):
-//   reach 0.40 of each axis: 80^3 x 78 bands 517 -> 915 us, 96 x 72 x 96 x 60 546 -> 1093,
-//     64^3 x 152 547 -> 718, 128 x 64 x 128 x 38 723 -> 973; but 48^3 0.74 of the time,
-//     and with y codelets of 15 points 64 x 150 x 64 0.90, 72 x 135 x 64 0.73;
-//   reach 0.12: 96 x 72 x 96 257 -> 344, 108 x 90 x 64 233 -> 328, 120 x 80 x 64 239 ->
-//     309; but 80^3 0.91, 64^3 0.60, 96 x 32 x 64 0.70, 128^2 x 16 0.79, 120^2 x 64 0.90.
+// and from Q = 15 on the lane quads spill as well (56 registers per lane; 120 and more
+// at Q = 24 to 27), except in the density alone.  Whole calls on the layout's kernel ->
+// on lane quads, FP64 (many bands; a ratio where they are faster):
+//   reach 0.40 of each axis: 80^3 x 78 bands 516 -> 915 us, 96 x 72 x 96 x 60 541 -> 1093,
+//     64^3 x 152 442 -> 718, 128 x 64 x 128 x 38 723 -> 978; but 48^3 0.74 of the time,
+//     and with codelets of 15 or 16 points 64 x 150 x 64 0.90, 72 x 135 x 64 0.73, 128 x
+//     18 x 64 0.75;
+//   reach 0.12: 96 x 72 x 96 252 -> 344, 108 x 90 x 64 223 -> 328, 120 x 80 x 64 229 ->
+//     309, parted 108^2 x 64 300 -> 421; but 80^3 0.91, 64^3 0.60, 96 x 32 x 64 0.70,
+//     128^2 x 16 0.79, 120^2 x 64 0.90;
+//   density alone, reach 0.40: 72^3 0.87 of the time on the layout's kernel, 80^3 0.84,
+//     120 x 80 x 64 0.82; on lane quads 60^3 0.78, 100^3 0.79, 128 x 64 x 128 0.88.
 // With masks, two waves per SIMD want workgroups that fill them: 120 x 80 x 64 x 65 bands,
-// reach 0.25, five waves on a CU, 1.13 times the time.
-inline bool lq_pays(const Geometry &g, const LaneQuads &lq, double ext)
+// reach 0.25, five waves on a CU, 1.18 times the time.
+inline bool lq_pays(const Geometry &g, const LaneQuads &lq, double ext, int mode)
 {
     const int codelet = std::max(std::max(g.L1x, g.L2x), std::max(g.L1y, g.L2y));
-    const bool slow = g.full == 4 || codelet > 12; // the layout's own kernel
+    const bool two = lq_wpe(MODE_APPLY, lq.q, lq_ymax(g)) == 2; // 256 registers
+    const bool parted = g.full == 4, dens = mode == MODE_DENSITY;
     if (lq.cls) {
         const LqLaunch l = lq_launch(g, lq, MODE_APPLY, 4);
         const int waves = l.threads / 64 * std::max(1, l.resident / std::max(1, lq.cus));
-        return slow || lq_wpe(MODE_APPLY, lq.q, lq_ymax(g)) > 2 || 3 * waves > 16;
+        return parted || codelet > 12 || !two || 3 * waves > 16;
     }
-    if (ext < 0.25 * g.N1) return lq.q <= 20 || slow || g.N2 <= 32;
-    return lq.q <= 12 || (lq.q <= 18 && codelet > 12);
+    if (ext < 0.25 * g.N1)
+        return dens || lq.q <= 20 || codelet > 12 || g.N2 <= 32 || (parted && two);
+    if (dens) return lq.q <= 16 || codelet > 12 || parted;
+    return lq.q <= 12 || (codelet > 12 && (lq.q <= 18 || g.N2 <= 24));
 }
 // Whole-plane kernels with a compiled x split and the y split at run time; hit =
 // false where none applies.

@@ -40,23 +40,31 @@ int main()
     const struct {
         int n[3];
         double f;
-        bool pays;
+        bool pays, dens;
     } shapes[] = {
-        {{80, 80, 80}, 0.4, false},   {{96, 72, 96}, 0.4, false},  {{96, 80, 96}, 0.4, false},
-        {{108, 90, 64}, 0.4, false},  {{100, 36, 100}, 0.4, false}, {{64, 64, 64}, 0.4, false},
-        {{128, 64, 128}, 0.4, false}, {{96, 72, 96}, 0.12, false}, {{108, 90, 64}, 0.12, false},
-        {{120, 80, 64}, 0.12, false}, {{120, 80, 64}, 0.25, false}, {{32, 32, 32}, 0.4, true},
-        {{48, 48, 48}, 0.4, true},    {{72, 135, 64}, 0.4, true},  {{64, 150, 64}, 0.4, true},
-        {{32, 64, 64}, 0.12, true},   {{80, 80, 80}, 0.12, true},  {{96, 32, 64}, 0.12, true},
-        {{128, 128, 16}, 0.12, true}, {{64, 64, 64}, 0.25, true},  {{80, 80, 80}, 0.25, true},
-        {{96, 96, 96}, 0.25, true},   {{128, 128, 128}, 0.25, true}, {{60, 60, 100}, 0.25, true},
-        {{120, 120, 64}, 0.25, true}, {{128, 72, 128}, 0.25, true},
+        {{80, 80, 80}, 0.4, false, false},    {{96, 72, 96}, 0.4, false, false},
+        {{96, 80, 96}, 0.4, false, false},    {{108, 90, 64}, 0.4, false, false},
+        {{100, 36, 100}, 0.4, false, false},  {{64, 64, 64}, 0.4, false, true},
+        {{128, 64, 128}, 0.4, false, true},   {{100, 100, 100}, 0.4, false, true},
+        {{96, 72, 96}, 0.12, false, true},    {{108, 90, 64}, 0.12, false, true},
+        {{108, 108, 64}, 0.12, false, true},  {{120, 80, 64}, 0.12, false, true},
+        {{120, 80, 64}, 0.25, false, false},  {{32, 32, 32}, 0.4, true, true},
+        {{48, 48, 48}, 0.4, true, true},      {{72, 135, 64}, 0.4, true, true},
+        {{64, 150, 64}, 0.4, true, true},     {{32, 64, 64}, 0.12, true, true},
+        {{80, 80, 80}, 0.12, true, true},     {{96, 32, 64}, 0.12, true, true},
+        {{128, 128, 16}, 0.12, true, true},   {{64, 64, 64}, 0.25, true, true},
+        {{80, 80, 80}, 0.25, true, true},     {{96, 96, 96}, 0.25, true, true},
+        {{128, 128, 128}, 0.25, true, true},  {{60, 60, 100}, 0.25, true, true},
+        {{120, 120, 64}, 0.12, true, true},   {{128, 72, 128}, 0.25, true, true},
+        {{128, 18, 64}, 0.4, true, true},
     };
     for (const auto &s : shapes) {
         Geometry g;
         LaneQuads lq;
         HostPlan h;
-        if (!setup(s.n, s.f, g, lq, h) || lq_pays(g, lq, s.f * s.n[0]) != s.pays) {
+        if (!setup(s.n, s.f, g, lq, h) ||
+            lq_pays(g, lq, s.f * s.n[0], MODE_APPLY) != s.pays ||
+            lq_pays(g, lq, s.f * s.n[0], MODE_DENSITY) != s.dens) {
             std::printf("lq_pays %d x %d x %d reach %.2f\n", s.n[0], s.n[1], s.n[2], s.f);
             ++bad;
         }
