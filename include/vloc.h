@@ -101,13 +101,20 @@ typedef struct {
                                  plane leaves one workgroup per CU (more than
                                  80 KiB of LDS), the application runs 1024, and
                                  so do the density kernels of the compiled 128^2
-                                 planes (when plane_threads >= 512)              */
+                                 planes (when plane_threads >= 512); compiled FP32
+                                 planes of which two fit a CU (72 x 96, 80^2, 96^2)
+                                 run 768 for the application and the density (when
+                                 plane_threads >= 512); and a whole-plane launch
+                                 never has more threads than its widest stage has
+                                 tasks (in steps of 256).  A value other than 0
+                                 keeps the layout's own kernel (see plane_xmode)  */
     int32_t plane_xwaves;     /* wavefronts of the plane workgroup that run the x
                                  pass (each with its own row buffer); 0 = auto     */
     int32_t plane_xmode;      /* layout of the plane kernel: 0 = automatic (3 where
                                  the whole plane fits in LDS, else 6, else 1; FP64
                                  application and density then run the lane-quad
-                                 kernel where N1 / 4 is a codelet of 8 to 32 points,
+                                 kernel where N1 / 4 is a codelet of 8 to 32 points
+                                 and it is the faster one for the sphere's reach,
                                  unless plane_threads, plane_rows, plane_xwaves or an
                                  x or y split is given as well); 1 = the
                                  occupied x-planes plus per-wavefront row buffers;
@@ -230,7 +237,10 @@ vloc_status vloc_plan_stick_groups(vloc_plan plan, int32_t *group_of_stick);
  * sticks_per_group, band_chunk}; out[8..13] = {plane_rows, plane_threads,
  * plane_lds_bytes, nxo, plane_xwaves, plane_xmode} where nxo is the number of
  * occupied x-planes and plane_xmode is 1 (row buffers), 2 (lane quads), 3, 4 or 5
- * (whole plane) or 6 (parted plane; plane_rows is then the rows per part). */
+ * (whole plane) or 6 (parted plane; plane_rows is then the rows per part).  On
+ * automatic FP64 schedules that run the lane-quad kernel (vloc_options.plane_xmode)
+ * the plane figures are those of the layout's own kernel, which the diagnostic
+ * transforms run, not those of the application's launches. */
 vloc_status vloc_plan_layout(vloc_plan plan, int32_t out[14]);
 
 /* ------------------------------------------------------- kernel timing */

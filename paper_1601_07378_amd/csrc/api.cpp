@@ -444,7 +444,8 @@ vloc_status upload(Engine &E)
             }
         }
         if (h.plane_full == 4) {
-            // one scratch region per workgroup of the persistent plane grid
+            // one scratch region per workgroup of the persistent plane grid (where the
+            // lane quads run the application, the diagnostic transforms still use it)
             const size_t pb = (size_t)g.resident_plane_wgs * h.nxo * h.grid[1] * h.elem_bytes();
             if ((e = hipMalloc(&E.d_parts, pb)) != hipSuccess) goto devfail;
         }

@@ -2633,8 +2633,8 @@ static hipError_t launch_plane_parts(const Geometry &g, const DevTables &t, cons
                            reinterpret_cast<cx<T> *>(psi), (long long)band0);
         return hipGetLastError();
     };
-    // FP64 density, x split 8 x 16, y split 16 x 8, two parts: the density sums
-    // stay in registers over a work item (512 threads, so 256 registers per
+    // FP64 density, x split 8 x 16, y split 16 x 8, two parts (with an explicit
+    // layout; automatic schedules run the lane quads): the density sums stay in registers over a work item (512 threads, so 256 registers per
     // thread; one x stage-B task per thread and part, the held y stage-B lines
     // in at most two rounds)
     if constexpr (std::is_same<T, double>::value &&
@@ -2718,7 +2718,7 @@ hipError_t launch_plane_full_mode(const Geometry &g, const DevTables &t, const L
 // for spheres of at least 0.36 of the x axis (any other plan runs the runtime-sized
 // kernel).  No zero masks: folding known zeros changes which products the compiler
 // fuses, and these kernels keep the bits of the runtime-sized ones, so that a
-// batch member equals its own plan whichever of them runs.  The x pass is two thirds
+// batch member equals its own plan whichever of the two runs.  The x pass is two thirds
 // of a plane's arithmetic, so most of what both compiled splits give: whole
 // applications FP32 60^3 x 555 bands 634 -> 568 us, 90 x 108 x 125 x 61 382 -> 367 us,
 // FP64 50^3 x 960 930 -> 889 us.  FP64 planes of an x axis that the lane-quad kernel
@@ -2931,7 +2931,10 @@ hipError_t launch_plane_full_tuned(const Geometry &g, const DevTables &t, const 
 #endif
 
 #if defined(VLOC_PART_COMMON)
-// Does a specialisation of both splits run this plan (or may one of the tuner's)?
+// Does a specialisation of both splits run this plan, or may one of the tuner's?  (The
+// tuner's plane lengths count as a whole, so planes of those lengths that no
+// specialisation fits, for instance 96 x 128, or 96 x 96 with a sphere beyond a quarter
+// of the axis, run the runtime-sized kernel and not the x lines.)
 static bool full_spec(const Geometry &g)
 {
 #define VLOC_FULL_HAVE(X1, X2, Y1, Y2, ZX, FX, ZY)                                                 \

@@ -23,8 +23,9 @@
 // 96 x 96 planes fit one CU, and a 128 x 128 plane fits without parts), and what
 // is left is vector issue (10.5k wave instructions per 96 x 96 plane, a lane swap
 // taking two slots: 62% of a CU's busy cycles) and waits: at four registers per point
-// only two or three waves fit a SIMD.  Runtime y sizes cost little, since the x pass,
-// two thirds of the arithmetic, is compiled for every Q.
+// two or three waves fit a SIMD beyond Q = 16, four up to there.  The y split is
+// compiled for four planes only (VLOC_LQ_YSPLITS); elsewhere the y sizes are runtime
+// values, and the x pass, two thirds of the arithmetic, is compiled for every Q.
 // Whole applications, quarter sphere, rows in LDS -> lane quads (with the other steps
 // of a call as they are now): 36^3 x 2572 bands 2204 -> 948 us, 48^3 x 1085 1496 -> 759,
 // 60^3 x 555 1289 -> 684, 64^3 x 457 1114 -> 689, 72^3 x 321 1112 -> 949, 80^3 x 1001
