@@ -276,6 +276,7 @@ vloc_status upload(Engine &E)
     if (e != hipSuccess || ndev < 1) return fail(VLOC_E_DEVICE, "no HIP device available");
     if ((e = hipGetDevice(&E.device)) != hipSuccess) return hip_fail(e, "hipGetDevice");
 
+    const size_t vt_bytes = (size_t)h.grid[0] * h.grid[1] * h.grid[2] * (h.elem_bytes() / 2);
     // member tables, concatenated: slots and groups relative to the member
     std::vector<int4> slot, gam;
     std::vector<int2> groups, cols;
@@ -354,6 +355,8 @@ vloc_status upload(Engine &E)
     if (!gam.empty() && (e = upload_vec(E.d_gam, gam)) != hipSuccess) goto devfail;
     if (!yslot.empty() && (e = upload_vec(E.d_yslot, yslot)) != hipSuccess) goto devfail;
     if (!holes.empty() && (e = upload_vec(E.d_holes, holes)) != hipSuccess) goto devfail;
+    // (one order of the potential; the routes decide which, and whether both are needed)
+    if (h.plane_full && (e = hipMalloc(&E.d_VT[0], vt_bytes)) != hipSuccess) goto devfail;
     {
         const Split *sp[3] = {&h.sx, &h.sy, &h.sz};
         for (int a = 0; a < 3; ++a) {
@@ -437,10 +440,10 @@ vloc_status upload(Engine &E)
         g.resident_plane_wgs = cus * per_cu;
         set_routes(E, cus);
         if (h.plane_full) {
-            const size_t vbytes = (size_t)g.N1 * g.N2 * g.N3 * (h.elem_bytes() / 2);
+            if (E.routes[0].q) std::swap(E.d_VT[0], E.d_VT[1]);
             for (const LaneQuads &lq : E.routes) {
                 void *&vt = E.d_VT[lq.q != 0];
-                if (!vt && (e = hipMalloc(&vt, vbytes)) != hipSuccess) goto devfail;
+                if (!vt && (e = hipMalloc(&vt, vt_bytes)) != hipSuccess) goto devfail;
             }
         }
         if (h.plane_full == 4) {
@@ -532,6 +535,11 @@ struct Part {
     int nb;
 };
 
+// A launch and the route of its segments.
+struct Work : Launch {
+    int route = 0;
+};
+
 // Segment of member `member` for its launch bands [b0, b0 + nb): caller data
 // pointers of its first band, its stick-buffer offset and its table rows.  In
 // the real mode a launch band is a pair of the caller's bands.
@@ -572,7 +580,7 @@ void fill_seg(const Engine &E, int member, const void *in, void *out, int64_t nb
 // pair of the caller's bands.  Members of different routes never share a launch.
 // Returns the stick-buffer bytes of the largest chunk.
 size_t make_launches(const Engine &E, const void *const *in, void *const *out,
-                     const int64_t *nbands, int64_t chunk, std::vector<Launch> &ls,
+                     const int64_t *nbands, int64_t chunk, std::vector<Work> &ls,
                      int64_t own = 0, int64_t own_cap = 0)
 {
     ls.clear();
@@ -584,7 +592,7 @@ size_t make_launches(const Engine &E, const void *const *in, void *const *out,
     std::vector<Part> solo;
     auto emit = [&](std::vector<Part> &cur) {
         if (cur.empty()) return;
-        Launch L{};
+        Work L{};
         L.nseg = (int)cur.size();
         long long s_off = 0;
         int band_lo = 0, blk_lo = 0;
@@ -639,7 +647,7 @@ size_t make_launches(const Engine &E, const void *const *in, void *const *out,
 // V; G2R / R2G / DENSITY (one member) take psi / weights indexed from the
 // launch's first band.
 template <typename T>
-vloc_status run_launches(Engine &E, int mode, const Launch *ls, size_t nl, const void *V,
+vloc_status run_launches(Engine &E, int mode, const Work *ls, size_t nl, const void *V,
                          void *psi, const double *wts, hipStream_t st, bool timed, void *S,
                          void *const VT[2], bool arrange = true)
 {
@@ -654,7 +662,7 @@ vloc_status run_launches(Engine &E, int mode, const Launch *ls, size_t nl, const
     const bool ordered = (mode == MODE_APPLY || mode == MODE_APPLY_DENSITY) && g.full;
     bool have[2] = {!arrange, !arrange};
     for (size_t li = 0; li < nl; ++li) {
-        const Launch &L = ls[li];
+        const Work &L = ls[li];
         const LaneQuads &lq = mode == MODE_DENSITY ? E.dens : E.routes[L.route];
         void *vt = VT[lq.q != 0];
         hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -691,7 +699,7 @@ vloc_status dispatch(vloc_plan p, int mode, const void *in, int64_t nbands, cons
     Engine &E = p->eng;
     vloc_status s = upload(E);
     if (s != VLOC_OK) return s;
-    std::vector<Launch> ls;
+    std::vector<Work> ls;
     const void *ins[1] = {mode == MODE_R2G ? nullptr : in};
     void *outs[1] = {(mode == MODE_APPLY || mode == MODE_R2G || mode == MODE_APPLY_DENSITY)
                          ? out
@@ -880,13 +888,12 @@ vloc_status vloc_apply_noalloc(vloc_plan plan, const void *c, int64_t nbands, co
     const int64_t chunk = (units + nch - 1) / nch;
     const bool f32 = h.opt.precision == VLOC_F32;
     for (int64_t b0 = 0, i = 0; b0 < units; b0 += chunk, ++i) {
-        Launch L{};
+        Work L{};
         const int nb = (int)std::min<int64_t>(chunk, units - b0);
         L.nseg = 1;
         fill_seg(E, 0, c, out, nbands, b0, nb, 0, 0, 0, L.seg[0]);
         L.nbt = nb;
         L.nblk = nb * h.ngroups;
-        L.route = 0;
         // the first chunk arranges the potential into VT (whole-plane layout);
         // the later ones read it from there
         s = f32 ? run_launches<float>(E, MODE_APPLY, &L, 1, V, nullptr, nullptr, E.stream, false,
@@ -1365,7 +1372,7 @@ vloc_status vloc_batch_apply(vloc_batch batch, const void *const *c, const int64
         if (nbands[i] < own) shared += nbands[i];
     const int64_t nch = std::max<int64_t>(1, (shared + cmax - 1) / cmax);
     const int64_t chunk = std::max<int64_t>(1, (shared + nch - 1) / nch);
-    std::vector<Launch> ls;
+    std::vector<Work> ls;
     size_t need = make_launches(E, c, out, nbands, chunk, ls, own, cmax);
     if ((s = ensure_scratch(E, need)) != VLOC_OK) return s;
     const bool f32 = h0.opt.precision == VLOC_F32;
